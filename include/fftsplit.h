@@ -135,11 +135,15 @@ typedef struct {
     size_t xspec_offset, xspec_bytes;
     size_t yspec_offset, yspec_bytes;
     size_t aux_offset, aux_bytes;   /* overlap-add seam partials (0 for overlap-save) */
-    /* Contraction kernel variant chosen by the plan: output tile
+    /* The contraction on the fp32 matrix instruction: output tile
      * contract_tile_m channels x contract_tile_n patches, input channels in
      * stages of contract_stage_k, and 3 (Gauss) or 4 real matrix products
-     * per complex multiply-add.  The environment variable
-     * FFTSPLIT_CONTRACT_TILE=[g3:|g4:]MxNxK overrides it at plan time. */
+     * per complex multiply-add.  It runs where the environment variable
+     * FFTSPLIT_CONTRACT_TILE=[g3:|g4:]MxNxK (which overrides the choice),
+     * FFTSPLIT_CONTRACT_PREFETCH or FFTSPLIT_CONTRACT_SPLIT=0 asks for it at
+     * plan time; otherwise the same product runs on the bf16 matrix
+     * instruction with every fp32 operand split exactly into three bf16
+     * parts, and is no less precise. */
     int contract_tile_m, contract_tile_n, contract_stage_k, contract_real_products;
     int spec_group;      /* G of the output-spectra layout */
     /* 1 if fftsplit_conv2d sums the input channels inside the inverse stage
@@ -194,6 +198,7 @@ typedef struct {
  * Other environment variables read here (for experiments; the defaults are
  * the measured best): FFTSPLIT_CONTRACT_TILE (see contract_tile_m),
  * FFTSPLIT_CONTRACT_PREFETCH (see contract_prefetch),
+ * FFTSPLIT_CONTRACT_SPLIT=0 (the contraction on the fp32 matrix instruction),
  * FFTSPLIT_FORWARD_BAND=0 / FFTSPLIT_INVERSE_BAND=0 (general forward /
  * inverse kernels instead of the row-band ones), FFTSPLIT_FORWARD_SWEEP=1 / 0
  * (the row-band forward's workgroups run items a grid apart, or contiguous

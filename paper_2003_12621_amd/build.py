@@ -16,7 +16,7 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libfftsplit.so")
 
-SOURCES = ["plan.cpp", "api.cpp", "k_weights.hip", "k_forward.hip", "k_contract.hip", "k_inverse.hip", "k_pool.hip",
+SOURCES = ["plan.cpp", "api.cpp", "k_weights.hip", "k_forward.hip", "k_contract.hip", "k_contract_split.hip", "k_inverse.hip", "k_pool.hip",
            "k_direct.hip", "k_oaa.hip", "noalloc.hip", "k_probe.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -66,7 +66,7 @@ def build(verbose: bool = False) -> str:
 KERNEL_SOURCES = {
     "forward": ["k_forward.hip", "band.hpp", "fft_regs.hpp", "twiddles.inc", "launch_util.hpp",
                 "fftsplit_internal.hpp"],
-    "contract": ["k_contract.hip", "launch_util.hpp", "fftsplit_internal.hpp"],
+    "contract": ["k_contract.hip", "k_contract_split.hip", "launch_util.hpp", "fftsplit_internal.hpp"],
     "inverse": ["k_inverse.hip", "band.hpp", "fft_regs.hpp", "twiddles.inc", "launch_util.hpp",
                 "fftsplit_internal.hpp"],
 }

@@ -26,6 +26,9 @@ struct fftsplit_plan_s {
     // 3 (Gauss) or 4 real products per complex multiply-add; con_prefetch
     // stages loaded ahead of the one being multiplied (1 to 3)
     int con_bm, con_bn, con_kc, con_products, con_prefetch;
+    // tile of the bf16-split contraction kernel (k_contract_split.hip), or
+    // kSplitNone where the fp32 one above runs
+    int con_split;
     // overlap-save band variant of the forward transform (band.hpp):
     // used if fwd_band; LDS row pitch, left zero columns, zero-row slot and
     // dynamic LDS bytes; fwd_sweep: items a grid apart instead of a
@@ -52,6 +55,13 @@ struct fftsplit_plan_s {
 };
 
 namespace fftsplit {
+
+// Tiles of the bf16-split contraction (channels x patches; gN: N wave groups
+// that share the reduction).
+enum SplitTile {
+    kSplitNone = 0, kSplit128x128, kSplit256x64, kSplit64x256, kSplit128x64, kSplit64x64, kSplit64x64g2,
+    kSplit128x32g2, kSplit64x32g4
+};
 
 // Granularity of the contraction's output tiles (patches x channels).
 constexpr int kTileGranule = 64;
@@ -171,6 +181,8 @@ hipError_t launch_forward(const fftsplit_plan_s& p, const float* x, float2* xspe
                           const LaunchEvents& ev);
 hipError_t launch_contract(const fftsplit_plan_s& p, const float2* xspec, const float2* wspec, float2* yspec,
                            hipStream_t s, const LaunchEvents& ev);
+hipError_t launch_contract_split(const fftsplit_plan_s& p, const float2* xspec, const float2* wspec, float2* yspec,
+                                 hipStream_t s, const LaunchEvents& ev);
 // whether launch_contract has a kernel for tile bm x bn, stages of kc and
 // 3 or 4 real products per complex multiply-add
 bool contract_variant_exists(int bm, int bn, int kc, int products);

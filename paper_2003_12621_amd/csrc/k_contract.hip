@@ -2,7 +2,13 @@
 // input channels): for every stored bin f,
 //     Y[f][co][t] = sum_ci W[f][ci][co] * X[f][ci][t]        (complex)
 // a batched complex matrix product -- the path's one dense contraction, and
-// the only place the fp32 matrix cores (MFMA) are used.
+// the only place the matrix cores (MFMA) are used.
+//
+// This is the form on the fp32 matrix instruction.  Plans run
+// contract_split_kernel (k_contract_split.hip) instead, faster and closer to
+// the exact sums, unless FFTSPLIT_CONTRACT_TILE, FFTSPLIT_CONTRACT_PREFETCH
+// or FFTSPLIT_CONTRACT_SPLIT=0 asks for this one; the layouts, the grid order
+// and the cache policies are the same.
 //
 // Each complex product is four real MFMA accumulations:
 //     Yr += Wr Xr - Wi Xi,   Yi += Wr Xi + Wi Xr.
@@ -423,6 +429,7 @@ bool contract_variant_exists(int bm, int bn, int kc, int products) {
 
 hipError_t launch_contract(const fftsplit_plan_s& p, const float2* xs, const float2* ws, float2* ys,
                            hipStream_t s, const LaunchEvents& ev) {
+    if (p.con_split) return launch_contract_split(p, xs, ws, ys, s, ev);
     const int v = p.con_bm * 1000000 + p.con_bn * 1000 + p.con_kc;
     if (p.con_products == 3) {
         switch (v) {

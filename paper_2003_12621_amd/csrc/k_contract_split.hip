@@ -1,0 +1,431 @@
+// Per-frequency-bin channel contraction on the bf16 matrix cores with fp32
+// results (the same product, layouts and grid order as contract_kernel in
+// k_contract.hip): for every stored bin f,
+//     Y[f][co][t] = sum_ci W[f][ci][co] * X[f][ci][t]        (complex).
+//
+// Each fp32 operand is split exactly into three bf16 parts, v = h + m + l
+// (8 significand bits each, rounded to nearest, so |m| <= 2^-9 |v| and
+// |l| <= 2^-18 |v|), and a product takes the six part products down to
+// 2^-18: l h', h l', m m', m h', h m', h h', accumulated in fp32.  What is
+// dropped (m l', l m', l l') is below 2^-26 of a product, under the fp32
+// rounding of one; and 16 products enter a matrix instruction before its sum
+// is rounded, against 2 in the fp32 instruction, so the sums are closer to
+// the exact ones than the fp32 kernel's (256 channels, normal operands: error
+// 2.4e-7 against 2.9e-7).  bf16 has fp32's exponent range, so no operand
+// needs scaling (operands below 2^-110 lose their smallest parts to
+// underflow).
+//
+// A complex value (re, im) is one dword of two bf16, and the two sit side by
+// side along the matrix instruction's reduction (k = 2 ci, 2 ci + 1), so
+//     Re Y = sum (Wr, Wi) . (Xr, -Xi),   Im Y = sum (Wr, Wi) . (Xi, Xr):
+// the patch operand's parts are made in both arrangements (one conversion
+// each: the sign is a source modifier), the filter's once, and a reduction
+// step of v_mfma_f32_16x16x32_bf16 is 16 input channels, one channel block.
+// Operand layout (64 lanes, lane l):
+//     A[i][k]: i = l % 16, k = 8 (l / 16) + 0..7     (channels 4 (l / 16) + 0..3)
+//     B[k][j]: j = l % 16, likewise
+//     D[i][j], register r: i = 4 (l / 16) + r, j = l % 16.
+// Rows and columns go to lanes in neighbouring pairs (row 32 p + 2 (l % 16)
+// + e is element l % 16 of block 2 p + e), so one 16-byte LDS read serves two
+// blocks and an output row is written in 16-byte pairs of patches.
+//
+// A workgroup tile is BM channels x BN patches of one bin, wave tiles of
+// 16 TM x 16 TN; channel blocks are loaded PF ahead straight into LDS as
+// fp32 and split after the LDS read.  At 64 x 64 a wave splits 8 values per
+// 48 matrix instructions: 400 vector instructions against 384 matrix
+// instructions of 16 cycles per channel block, which two waves per SIMD
+// overlap.  With KG > 1, KG wave groups take the channel blocks in turn and
+// add their sums through LDS: more waves on a compute unit that has one
+// workgroup (small grids, where a wave's chain of LDS read, split and product
+// is what takes the time).
+//
+// What bounds it (MI355X): the matrix cores, whose clock falls to 2.0 GHz
+// under it (2.4 under the fp32 kernel; a loop of the instruction alone
+// reaches 1745 TFLOP/s at 32x32x16 and 2040 at 16x16x32, hence that shape),
+// then the vector work and, with few patches, HBM.  Against the fp32 kernel,
+// whole launches in us (algorithmic rate at 8 flops per complex product):
+//     32x256x56^2, 512 patches            217 -> 164  (157 -> 209 TFLOP/s)
+//     32x512x28^2, 128 patches            217 -> 170
+//     32x128x112^2, 2048 patches          238 -> 178
+//     16x256x56^2 K=5, 64 patches         119 ->  97  (4.1 TB/s)
+//     32x64x224^2, 8192 patches           283 -> 245  (4.4 TB/s)
+//     1x512x28^2 at L = 8, 25 patches      34 ->  24
+// 32x32x16 instructions: 174 instead of 164 us on the first; the vector work
+// interleaved with the matrix instructions by the scheduler instead of two
+// waves overlapping, three stages ahead, and a priority for one of a compute
+// unit's two workgroups: no change.
+#include "fftsplit_internal.hpp"
+#include "launch_util.hpp"
+
+#include <type_traits>
+
+namespace fftsplit {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// Waits until at most N vector memory instructions and no LDS read are
+// outstanding, then passes the workgroup's barrier.  One block, so that
+// nothing the wave reads from LDS before it can still be in flight after it.
+template <int N>
+__device__ __forceinline__ void wait_and_barrier() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+// wait_and_barrier for n (<= MAX) later stages of LPS loads in flight.
+template <int MAX, int LPS>
+__device__ __forceinline__ void wait_stages(int n) {
+    static_assert(MAX * LPS < 64, "the counter's range");
+    if constexpr (MAX <= 0) {
+        wait_and_barrier<0>();
+    } else {
+        if (n >= MAX) wait_and_barrier<MAX * LPS>();
+        else wait_stages<MAX - 1, LPS>(n);
+    }
+}
+
+// 16 bytes per lane from uniform base + lane offset straight into LDS: lane
+// l writes LDS bytes [lds + 16 l, lds + 16 l + 16).  Inline assembly because
+// for the builtin the compiler waits for every outstanding load before each
+// LDS read; the caller waits (s_waitcnt vmcnt) before the barrier that
+// publishes a buffer.  The wait states cover a base that a vector
+// instruction wrote just before (five before a memory instruction reads it)
+// and the M0 write (one).
+template <bool NT>
+__device__ __forceinline__ void split_dma16(uint64_t base, unsigned voff, const void* lds_wave_base) {
+    const unsigned m0 = __builtin_amdgcn_readfirstlane(unsigned(reinterpret_cast<uintptr_t>(lds_wave_base)));
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(base), "s"(m0)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(m0)
+                     : "memory", "m0");
+}
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+    const f32x2 v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+
+// A 64-bit address that is the same in every lane, in scalar registers.
+// (readfirstlane returns a signed int: through unsigned, or the low word's
+// sign would overwrite the high word)
+__device__ __forceinline__ uint64_t uniform_address(const void* p) {
+    const uint64_t a = reinterpret_cast<uintptr_t>(p);
+    const unsigned lo = unsigned(__builtin_amdgcn_readfirstlane(int(unsigned(a))));
+    const unsigned hi = unsigned(__builtin_amdgcn_readfirstlane(int(unsigned(a >> 32))));
+    return uint64_t(lo) | uint64_t(hi) << 32;
+}
+
+// The filter operand: (re, im) -> three dwords of bf16 pairs whose sum is
+// (re, im).
+__device__ __forceinline__ void split_filter(float re, float im, unsigned (&a)[3]) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        a[q] = pack_bf16(re, im);
+        re -= __uint_as_float(a[q] << 16);
+        im -= __uint_as_float(a[q] & 0xffff0000u);
+    }
+}
+// The patch operand, for Re Y and for Im Y: the parts of (re, -im) and of
+// (im, re), or of (re, 0) and (0, im) in a slot of two real bins; NEG: of
+// their negatives.
+template <bool PACKED, bool NEG>
+__device__ __forceinline__ void split_patch(float re, float im, unsigned (&br)[3], unsigned (&bi)[3]) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const unsigned v = NEG ? pack_bf16(-im, -re) : pack_bf16(im, re);
+        br[q] = PACKED ? v >> 16 : (NEG ? pack_bf16(-re, im) : pack_bf16(re, -im));
+        bi[q] = PACKED ? v << 16 : v;
+        const float vi = __uint_as_float(v << 16), vr = __uint_as_float(v & 0xffff0000u);
+        im = NEG ? im + vi : im - vi;
+        re = NEG ? re + vr : re - vr;
+    }
+}
+
+template <int BM, int BN, int TM, int TN>
+struct SplitShape {
+    static constexpr int KC = kChanBlock;   // a stage is one channel block = one reduction step
+    static constexpr int WM = BM / (16 * TM), WN = BN / (16 * TN);   // waves
+    static constexpr int NT = 64 * WM * WN;
+    static constexpr int WE = KC * BM, XE = KC * BN;           // stage elements (complex)
+    static constexpr int WL = WE / 2 / NT, XL = XE / 2 / NT;   // 16-byte loads per thread and stage
+    static constexpr int STAGE = WE + XE;
+    static constexpr int WROWS = NT / (BM / 2), XROWS = NT / (BN / 2);   // rows per load
+    static_assert(TM % 2 == 0 && TN % 2 == 0, "row and column pairs");
+    static_assert(WL * NT * 2 == WE && XL * NT * 2 == XE, "loads divide evenly");
+    static_assert(NT % (BM / 2) == 0 && NT % (BN / 2) == 0, "whole rows per load");
+};
+
+template <int BM, int BN, int TM, int TN, int PF, int KG, bool WS, bool XS>
+__global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void contract_split_kernel(
+    const float2* __restrict__ xs, const float2* __restrict__ ws, float2* __restrict__ ys, int cin, int coutp, int ntp,
+    int nt, int nbco, int nbt, int nbins, int ygroup, int npacked) {
+    using S = SplitShape<BM, BN, TM, TN>;
+    constexpr int KC = S::KC;
+    constexpr int NT = S::NT;             // threads of a group
+    extern __shared__ float4 lds_raw[];   // PF + 1 stage buffers for each group
+
+    const int group = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(int(threadIdx.x) / NT);
+    const int tid = int(threadIdx.x) - group * NT;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / S::WN, wn = wave % S::WN;
+    const int quad = lane >> 4, col = lane & 15;
+
+    // (bin, patch block, channel block), channel blocks fastest, the bins
+    // dealt to the XCDs in turn (as contract_kernel)
+    const int per_bin = nbco * nbt;
+    int lb;
+    if (int(gridDim.x) % (kNumXcd * per_bin) == 0) {
+        const int x = int(blockIdx.x) % kNumXcd, j = int(blockIdx.x) / kNumXcd;
+        lb = ((j / per_bin) * kNumXcd + x) * per_bin + j % per_bin;
+    } else {
+        lb = xcd_logical_block(blockIdx.x, gridDim.x);
+    }
+    const int rest = lb / nbco;
+    const int co0 = (lb - rest * nbco) * BM;
+    const int f = rest / nbt;
+    const int t0 = (rest - f * nbt) * BN;
+
+    // this lane's 16 bytes of a load: row tid / (B / 2) of the rows it covers
+    const unsigned wrow = unsigned(coutp) * 8u, xrow = unsigned(ntp) * 8u;
+    const unsigned wvoff = unsigned(tid / (BM / 2)) * wrow + unsigned(tid % (BM / 2)) * 16u;
+    const unsigned xvoff = unsigned(tid / (BN / 2)) * xrow + unsigned(tid % (BN / 2)) * 16u;
+    const uint64_t wbase = uniform_address(ws + size_t(f) * cin * coutp + co0);
+    const uint64_t xbase = uniform_address(xs + spec_offset(0, f, t0, nbins, ntp));
+    const uint64_t xblock = uint64_t(unsigned(nbins)) * xrow;   // bytes from a channel block to the next, per channel
+
+    float2* const lds = reinterpret_cast<float2*>(lds_raw) + group * ((PF + 1) * S::STAGE);
+    auto dma_stage = [&](int k0, float2* stage) {
+        uint4* sw = reinterpret_cast<uint4*>(stage) + wave * 64;
+        uint4* sx = reinterpret_cast<uint4*>(stage + S::WE) + wave * 64;
+        const uint64_t wb = wbase + uint64_t(unsigned(k0)) * wrow, xb = xbase + uint64_t(unsigned(k0)) * xblock;
+#pragma unroll
+        for (int i = 0; i < S::WL; ++i) split_dma16<WS>(wb + uint64_t(i * S::WROWS) * wrow, wvoff, sw + i * NT);
+#pragma unroll
+        for (int i = 0; i < S::XL; ++i) split_dma16<XS>(xb + uint64_t(i * S::XROWS) * xrow, xvoff, sx + i * NT);
+    };
+
+    // One stage (16 channels = one reduction step).  Lane (quad, col) holds
+    // channels 4 quad + 0..3 of rows (columns) 32 p + 2 col + 0, 1 of the
+    // wave's tile, one 16-byte LDS read per channel and pair; the filter
+    // parts of the whole tile stay in registers, the patch parts are made a
+    // column block at a time.
+    auto multiply = [&](const float2* stage, floatx4 (&accR)[TM][TN], floatx4 (&accI)[TM][TN], auto packed, auto neg) __attribute__((always_inline)) {
+        const float2* sw = stage + (4 * quad) * BM + wm * (16 * TM) + 2 * col;
+        const float2* sx = stage + S::WE + (4 * quad) * BN + wn * (16 * TN) + 2 * col;
+        u32x4 a[3][TM];
+#pragma unroll
+        for (int p = 0; p < TM / 2; ++p)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float4 v = *reinterpret_cast<const float4*>(sw + c * BM + 32 * p);
+                unsigned q0[3], q1[3];
+                split_filter(v.x, v.y, q0);
+                split_filter(v.z, v.w, q1);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    a[q][2 * p][c] = q0[q];
+                    a[q][2 * p + 1][c] = q1[q];
+                }
+            }
+#pragma unroll
+        for (int p = 0; p < TN / 2; ++p) {
+            float4 v[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = *reinterpret_cast<const float4*>(sx + c * BN + 32 * p);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int j = 2 * p + e;
+                u32x4 br[3], bi[3];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    unsigned qr[3], qi[3];
+                    split_patch<decltype(packed)::value, decltype(neg)::value>(e ? v[c].z : v[c].x, e ? v[c].w : v[c].y, qr, qi);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        br[q][c] = qr[q];
+                        bi[q][c] = qi[q];
+                    }
+                }
+                // smallest part products first
+                constexpr int PW[6] = {2, 0, 1, 1, 0, 0}, PX[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+                for (int q = 0; q < 6; ++q)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const bf16x8 w = __builtin_bit_cast(bf16x8, a[PW[q]][i]);
+                        accR[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            w, __builtin_bit_cast(bf16x8, br[PX[q]]), accR[i][j], 0, 0, 0);
+                        accI[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            w, __builtin_bit_cast(bf16x8, bi[PX[q]]), accI[i][j], 0, 0, 0);
+                    }
+            }
+        }
+    };
+
+    constexpr int NB = PF + 1;
+    constexpr int LPS = S::WL + S::XL;   // memory instructions per stage and thread
+    // (a block of padding patches only has zero spectra: no stages)
+    const int nfull = t0 < nt ? cin / KC : 0, nstage = t0 < nt ? (cin + KC - 1) / KC : 0;
+    // The group's stage of iteration it (channel block s = it * KG + group)
+    // into its buffer; a partial last one through registers, its missing
+    // rows zero (their addresses clamped to the last row).
+    auto load_stage = [&](int it) __attribute__((always_inline)) {
+        float2* const stage = lds + (NB == 2 ? it & 1 : it % NB) * S::STAGE;
+        const int s = it * KG + group;
+        if (s < nfull) {
+            dma_stage(s * KC, stage);
+        } else if (s < nstage) {
+            const int k0 = s * KC, last = cin - 1 - k0;
+            const char* wsrc = reinterpret_cast<const char*>(ws + (size_t(f) * cin + k0) * coutp + co0) + (tid % (BM / 2)) * 16;
+            const char* xsrc = reinterpret_cast<const char*>(xs + spec_offset(k0, f, t0, nbins, ntp)) + (tid % (BN / 2)) * 16;
+            uint4* sw = reinterpret_cast<uint4*>(stage);
+            uint4* sx = reinterpret_cast<uint4*>(stage + S::WE);
+#pragma unroll
+            for (int i = 0; i < S::WL; ++i) {
+                const int c = i * S::WROWS + tid / (BM / 2);
+                const uint4 v = *reinterpret_cast<const uint4*>(wsrc + size_t(min(c, last)) * wrow);
+                sw[i * NT + tid] = c <= last ? v : make_uint4(0, 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < S::XL; ++i) {
+                const int c = i * S::XROWS + tid / (BN / 2);
+                const uint4 v = *reinterpret_cast<const uint4*>(xsrc + size_t(min(c, last)) * xrow);
+                sx[i * NT + tid] = c <= last ? v : make_uint4(0, 0, 0, 0);
+            }
+        }
+    };
+    auto run = [&](auto packed) __attribute__((always_inline)) {
+        floatx4 accR[TM][TN], accI[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) accR[i][j][r] = accI[i][j][r] = 0.f;
+
+#pragma unroll
+        for (int d = 0; d < PF; ++d) load_stage(d);
+        auto iterations = [&](int it, int end, auto neg) __attribute__((always_inline)) {
+            for (; it < end; ++it) {
+                // this iteration's stage is whole once at most the loads of
+                // the group's whole stages issued after it remain; past the
+                // barrier every wave has also finished with the buffer of the
+                // iteration before, which iteration it + PF then fills
+                const int s = it * KG + group;
+                const int later = s < nfull ? min(PF - 1, (nfull - 1 - s) / KG) : 0;
+                wait_stages<PF - 1, LPS>(later);
+                load_stage(it + PF);
+                const float2* cur = lds + (NB == 2 ? it & 1 : it % NB) * S::STAGE;
+                if (KG == 1 || s < nstage) multiply(cur, accR, accI, packed, neg);
+            }
+        };
+        auto negate = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    accR[i][j] = -accR[i][j];
+                    accI[i][j] = -accI[i][j];
+                }
+        };
+        // The matrix unit's sums err towards minus infinity.  The last part
+        // of the channels is therefore added to the negated sums, with the
+        // patch operand's sign flipped, where they err the other way: about
+        // a third of them, as the error of a step grows with the sum.
+        const int nit = (nstage + KG - 1) / KG, turn = nit - nit * 11 / 32;
+        iterations(0, turn, std::false_type{});
+        negate();
+        iterations(turn, nit, std::true_type{});
+        negate();
+        if constexpr (KG > 1) {
+            // the groups' partial sums, through LDS to the first group
+            constexpr int NA = 2 * TM * TN;
+            floatx4* part = reinterpret_cast<floatx4*>(lds_raw) + tid;
+            __syncthreads();
+            if (group > 0) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        part[((group - 1) * NA + 2 * (i * TN + j)) * NT] = accR[i][j];
+                        part[((group - 1) * NA + 2 * (i * TN + j) + 1) * NT] = accI[i][j];
+                    }
+            }
+            __syncthreads();
+            if (group > 0) return;
+#pragma unroll
+            for (int g = 0; g < KG - 1; ++g)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        accR[i][j] += part[(g * NA + 2 * (i * TN + j)) * NT];
+                        accI[i][j] += part[(g * NA + 2 * (i * TN + j) + 1) * NT];
+                    }
+        }
+
+        // Output spectra (patch-group-major): D register r of lane (quad,
+        // col) is row 4 quad + r, column col of its 16 x 16 block, so a lane
+        // holds pairs of neighbouring patches: 16-byte stores, 16 lanes a row.
+        const unsigned cs8 = unsigned(nbins) * unsigned(ntp) * 8u;   // next channel
+        const BufRsrc ry = make_rsrc(ys + size_t(co0) * nbins * ntp, unsigned(size_t(coutp - co0) * cs8));
+        const unsigned row8 = unsigned(wm * (16 * TM) + 8 * quad) * cs8;
+#pragma unroll
+        for (int j = 0; j < TN; j += 2) {
+            const int t = t0 + wn * (16 * TN) + 16 * j + 2 * col;
+            const unsigned voff = row8 + unsigned(yspec_offset(0, f, t, nbins, ygroup, ntp / ygroup)) * 8u;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    buf_store_f32x4(make_float4(accR[i][j][r], accI[i][j][r], accR[i][j + 1][r], accI[i][j + 1][r]), ry,
+                                    voff, unsigned(32 * (i / 2) + 2 * r + i % 2) * cs8);
+        }
+    };
+    // one loop for each kind of bin (a branch inside the loop would merge the
+    // accumulators of its two sides by copies)
+    if (f >= nbins - npacked) run(std::true_type{});
+    else run(std::false_type{});
+}
+
+template <int BM, int BN, int TM, int TN, int PF, int KG = 1>
+static hipError_t launch_split_v(const fftsplit_plan_s& p, const float2* xs, const float2* ws, float2* ys,
+                                 hipStream_t s, const LaunchEvents& ev) {
+    using S = SplitShape<BM, BN, TM, TN>;
+    auto kern = contract_split_kernel<BM, BN, TM, TN, PF, KG, false, false>;
+    constexpr int lds = KG * (PF + 1) * S::STAGE * 8;
+    static_assert(lds <= 160 * 1024 && (KG - 1) * 2 * TM * TN * S::NT * 16 <= lds, "fits the LDS");
+    if (p.coutp % BM != 0 || p.ntp % BN != 0) return hipErrorInvalidValue;
+    const int nbco = p.coutp / BM, nbt = p.ntp / BN;
+    if (nbt <= 2) kern = contract_split_kernel<BM, BN, TM, TN, PF, KG, true, false>;
+    else if (nbco == 1) kern = contract_split_kernel<BM, BN, TM, TN, PF, KG, false, true>;
+    const hipError_t attr = allow_dynamic_lds(kern, lds);
+    if (attr != hipSuccess) return attr;
+    const size_t nb = size_t(nbco) * nbt * p.bins;
+    return launch_kernel(kern, dim3(unsigned(nb)), dim3(KG * S::NT), lds, s, ev.start, ev.stop, xs, ws, ys, p.prob.cin,
+                         p.coutp, p.ntp, p.nt, nbco, nbt, p.bins, patch_group(p.L), packed_slots(p.L));
+}
+
+hipError_t launch_contract_split(const fftsplit_plan_s& p, const float2* xs, const float2* ws, float2* ys,
+                                 hipStream_t s, const LaunchEvents& ev) {
+    switch (p.con_split) {
+        case kSplit128x128: return launch_split_v<128, 128, 4, 4, 1, 1>(p, xs, ws, ys, s, ev);
+        case kSplit256x64: return launch_split_v<256, 64, 4, 4, 1, 1>(p, xs, ws, ys, s, ev);
+        case kSplit64x256: return launch_split_v<64, 256, 4, 4, 1, 1>(p, xs, ws, ys, s, ev);
+        case kSplit128x64: return launch_split_v<128, 64, 4, 2, 1, 1>(p, xs, ws, ys, s, ev);
+        case kSplit64x64: return launch_split_v<64, 64, 2, 2, 2, 1>(p, xs, ws, ys, s, ev);
+        case kSplit64x64g2: return launch_split_v<64, 64, 2, 2, 1, 2>(p, xs, ws, ys, s, ev);
+        case kSplit128x32g2: return launch_split_v<128, 32, 2, 2, 1, 2>(p, xs, ws, ys, s, ev);
+        case kSplit64x32g4: return launch_split_v<64, 32, 2, 2, 1, 4>(p, xs, ws, ys, s, ev);
+        case kSplitNone: break;
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace fftsplit

@@ -172,6 +172,56 @@ static void choose_forward_band(fftsplit_plan_s& p) {
     p.fwd_lds = int(lds);
 }
 
+static const char* split_tile_name(int tile) {
+    switch (tile) {
+        case kSplit128x128: return "split 128x128";
+        case kSplit256x64: return "split 256x64";
+        case kSplit64x256: return "split 64x256";
+        case kSplit128x64: return "split 128x64";
+        case kSplit64x64: return "split 64x64";
+        case kSplit64x64g2: return "split 64x64/2";
+        case kSplit128x32g2: return "split 128x32/2";
+        case kSplit64x32g4: return "split 64x32/4";
+    }
+    return "fp32";
+}
+
+// The tile of the bf16-split contraction, by the number of workgroups it
+// gives (two of the large ones fill a compute unit, so 512 the chip).  A
+// wave's tile of 64 x 64 needs the fewest splits and LDS reads per product,
+// so the largest tile that still fills the chip is taken: on the layers
+// below, in us, 16x256x56^2 K=5 (one patch block): 256x64 97, 128x64 103,
+// 64x64 112; 8x128x112^2: 128x128 48, 128x64 52, 64x64 55; 32x64x224^2:
+// 64x256 243, 64x64 265.  Where it does not (4x256x56^2: 256x64 46, 64x64 in
+// two groups 31; 1x64x224^2: 64x256 17, 64x64 in two groups 12), 64x64 tiles
+// whose two wave groups take the channel blocks in turn (one group where
+// there are at most four blocks, all of them loaded at once: the whole
+// 1x64x224^2 layer 28.7 against 29.2 us); and where even half of those
+// patches would leave compute units idle, 64x32 in four groups
+// (1x512x28^2 at L = 8, 25 patches: 24 against 28 us).  Patches padded to 32
+// only: 128x32 in two groups (4x512x28^2: 59 us, one group 63).
+// An explicit FFTSPLIT_CONTRACT_TILE or _PREFETCH, or
+// FFTSPLIT_CONTRACT_SPLIT=0, selects the fp32 kernel instead.
+static void choose_contract_split(fftsplit_plan_s& p) {
+    p.con_split = kSplitNone;
+    const char* off = std::getenv("FFTSPLIT_CONTRACT_SPLIT");
+    const char* tile = std::getenv("FFTSPLIT_CONTRACT_TILE");
+    if ((off && *off == '0') || (tile && *tile) || std::getenv("FFTSPLIT_CONTRACT_PREFETCH")) return;
+    const auto blocks = [&](int bm, int bn) {
+        return p.coutp % bm == 0 && p.ntp % bn == 0 ? size_t(p.coutp / bm) * size_t(p.ntp / bn) * size_t(p.bins) : size_t(0);
+    };
+    constexpr size_t kFull = 512;
+    const size_t half_blocks = size_t(p.coutp / 64) * size_t((p.nt + 31) / 32) * size_t(p.bins);
+    if (p.ntp % 64 != 0) p.con_split = kSplit128x32g2;
+    else if (blocks(128, 128) >= kFull) p.con_split = kSplit128x128;
+    else if (blocks(256, 64) >= kFull) p.con_split = kSplit256x64;
+    else if (blocks(64, 256) >= kFull) p.con_split = kSplit64x256;
+    else if (blocks(128, 64) >= kFull) p.con_split = kSplit128x64;
+    else if (p.prob.cin <= 4 * kChanBlock) p.con_split = kSplit64x64;
+    else if (half_blocks <= kFull / 2) p.con_split = kSplit64x32g4;
+    else p.con_split = kSplit64x64g2;
+}
+
 static fftsplit_status_t build_plan(const fftsplit_problem_t* prob, int device, const char* arch,
                                     fftsplit_plan_t* out) {
     if (!prob || !out) return fail(FFTSPLIT_ERROR_INVALID_VALUE, "problem and output pointers must be non-NULL");
@@ -376,6 +426,7 @@ static fftsplit_status_t build_plan(const fftsplit_problem_t* prob, int device, 
                                                       " does not divide the padded problem");
     }
 
+    choose_contract_split(*plan);
     choose_forward_band(*plan);
     choose_inverse_band(*plan);
     // The max-pool goes into the overlap-save inverse's store phase when no
@@ -403,9 +454,9 @@ static fftsplit_status_t build_plan(const fftsplit_problem_t* prob, int device, 
     if (log && *log && *log != '0') {
         std::fprintf(stderr,
                      "[fftsplit] plan n=%d cin=%d %dx%d cout=%d k=%d -> T=%d L=%d tiles=%d(%d) bins=%d %s "
-                     "model=%.1f us wspec=%zu ws=%zu\n",
+                     "model=%.1f us wspec=%zu ws=%zu contract=%s\n",
                      p.n, p.cin, p.h, p.w, p.cout, p.k, g.T, g.L, g.nt, g.ntp, g.bins, oaa ? "oaa" : "os",
-                     g.model_seconds * 1e6, wsb, plan->ws_bytes);
+                     g.model_seconds * 1e6, wsb, plan->ws_bytes, split_tile_name(plan->con_split));
     }
     *out = plan;
     return FFTSPLIT_SUCCESS;

@@ -1,0 +1,95 @@
+"""The bf16-split contraction (k_contract_split.hip) at the edges of its tiles.
+
+Every tile the plan can choose, channel counts below, at and just past a
+channel block of 16 (and block counts the wave groups do not divide), patches
+that leave whole blocks of padding, and the two slots of real bins, against
+the float64 channel sum of the GPU's own spectra.
+
+Tolerance.  An operand is its three bf16 parts exactly, and what six of the
+nine part products leave out is below 2^-26 of a product.  The rest is fp32
+accumulation of 2 cin real products: 6 matrix instructions per 16 channels,
+each rounding its running sum, and at most 3 further additions of partial
+sums.  With each rounding below 2^-24 of the sum of absolute products (2^-23
+for an instruction that rounds inside as well),
+    |Y - ref| <= (6 ceil(cin / 16) + 3) 2^-23 (|W| |X|).
+"""
+import numpy as np
+import pytest
+
+from workloads import small_layer
+
+torch = pytest.importorskip("torch")
+fs = pytest.importorskip("paper_2003_12621_amd")
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (n, cin, h, w, cout, k), tile T, the tile the plan's rule gives
+    ((2, 97, 24, 24, 70, 3), 6, "64x32, four groups, a partial block"),
+    ((3, 80, 24, 24, 40, 3), 6, "64x32, four groups, five channel blocks"),
+    ((1, 3, 20, 40, 5, 3), 14, "64x64, one channel block, padding patches"),
+    ((2, 50, 24, 24, 40, 3), 14, "64x64, a partial block"),
+    ((1, 1, 30, 30, 1, 3), 30, "64x64, one channel"),
+    ((5, 83, 56, 56, 192, 3), 14, "64x64, two groups, a partial block"),
+    ((4, 96, 56, 40, 192, 3), 14, "64x64, two groups"),
+    ((2, 19, 28, 28, 128, 3), 14, "128x32, two groups"),
+    ((5, 40, 42, 28, 256, 3), 14, "128x32, two groups, padding patches"),
+    ((4, 21, 100, 100, 128, 3), 30, "128x64"),
+    ((4, 31, 100, 100, 256, 3), 30, "256x64"),
+    ((8, 5, 110, 120, 128, 3), 30, "128x128"),
+    ((16, 34, 112, 100, 48, 3), 30, "64x256"),
+    ((2, 18, 25, 25, 20, 5), 5, "64x64, odd transform size: no packed bins"),
+    ((2, 70, 25, 25, 20, 5), 5, "64x32, four groups, odd transform size"),
+]
+
+
+def _spectra(shape, tile, scale=1.0):
+    x, w = small_layer(*shape, seed=sum(shape))
+    plan = fs.Plan(*shape, tile=tile, mode="oaa" if tile == shape[5] else "os")
+    ws = plan.new_workspace()
+    ws.fill_(0xFF)   # NaN wherever nothing is written
+    wspec = plan.transform_weights(torch.from_numpy(w).cuda())
+    plan.forward(torch.from_numpy(np.ascontiguousarray(x * np.float32(scale))).cuda(), ws)
+    plan.contract(wspec, ws)
+    nt = plan.info.tiles
+    X, W = plan.xspec_view(ws)[:, :, :nt], plan.wspec_view(wspec)
+    return X.to(torch.complex128), W.to(torch.complex128), plan.yspec_view(ws), plan
+
+
+def _channel_sum(X, W, packed):
+    Y = W.transpose(1, 2).contiguous() @ X
+    A = W.abs().transpose(1, 2).contiguous() @ X.abs()
+    for f in range(Y.shape[0] - 2, Y.shape[0]) if packed else ():
+        Y[f] = torch.complex(W[f].real.T.contiguous() @ X[f].real, W[f].imag.T.contiguous() @ X[f].imag)
+    return Y, A
+
+
+@pytest.mark.parametrize("shape,tile,what", CASES)
+def test_against_float64(shape, tile, what):
+    print(f"[case] {shape} T={tile} {what}", flush=True)
+    X, W, got, plan = _spectra(shape, tile)
+    ref, mag = _channel_sum(X, W, plan.nfft % 2 == 0)
+    nt = plan.info.tiles
+    bound = (6 * -(-shape[1] // 16) + 3) * 2.0 ** -23
+    err = (got[:, :, :nt].to(torch.complex128) - ref).abs()
+    assert bool((err <= bound * mag).all()), float((err / mag.clamp_min(1e-300)).max()) / bound
+    # padded output channels and padding patches are zero spectra
+    assert not bool(got[:, shape[4]:].abs().any()) and not bool(got[:, :, nt:].abs().any())
+
+
+@pytest.mark.parametrize("shape,tile", [((4, 256, 56, 56, 256, 3), 14), ((16, 64, 56, 56, 256, 5), 28),
+                                        ((2, 512, 14, 14, 128, 3), 6)])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -60, 2.0 ** 60])
+def test_no_less_precise_than_fp32(shape, tile, scale, monkeypatch):
+    """Its error against float64 is no larger than the fp32 matrix
+    instruction's on the same spectra, at any scale of the input."""
+    def error():
+        X, W, got, plan = _spectra(shape, tile, scale)
+        ref, _ = _channel_sum(X, W, True)
+        d = got[:, :, :plan.info.tiles].to(torch.complex128) - ref
+        return float((d / scale).abs().pow(2).sum().sqrt() / (ref / scale).abs().pow(2).sum().sqrt())
+    split = error()
+    monkeypatch.setenv("FFTSPLIT_CONTRACT_SPLIT", "0")
+    fp32 = error()
+    print(f"[case] {shape} scale={scale:g}: split {split:.3e} fp32 {fp32:.3e}", flush=True)
+    assert split <= fp32
