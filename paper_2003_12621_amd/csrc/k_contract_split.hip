@@ -200,14 +200,31 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
     const uint64_t xblock = uint64_t(unsigned(nbins)) * xrow;   // bytes from a channel block to the next, per channel
 
     float2* const lds = reinterpret_cast<float2*>(lds_raw) + group * ((PF + 1) * S::STAGE);
-    auto dma_stage = [&](int k0, float2* stage) {
+    // Channel block s into `stage`.  In a partial last one the missing rows
+    // are read from the last row (in range); the filter's are zeroed before
+    // they are used (below), so that what the patch rows hold does not count.
+    auto dma_stage = [&](int s, float2* stage) __attribute__((always_inline)) {
         uint4* sw = reinterpret_cast<uint4*>(stage) + wave * 64;
         uint4* sx = reinterpret_cast<uint4*>(stage + S::WE) + wave * 64;
+        const int k0 = s * KC, last = cin - 1 - k0;
         const uint64_t wb = wbase + uint64_t(unsigned(k0)) * wrow, xb = xbase + uint64_t(unsigned(k0)) * xblock;
+        if (last >= KC - 1) {
 #pragma unroll
-        for (int i = 0; i < S::WL; ++i) split_dma16<WS>(wb + uint64_t(i * S::WROWS) * wrow, wvoff, sw + i * NT);
+            for (int i = 0; i < S::WL; ++i) split_dma16<WS>(wb + uint64_t(i * S::WROWS) * wrow, wvoff, sw + i * NT);
 #pragma unroll
-        for (int i = 0; i < S::XL; ++i) split_dma16<XS>(xb + uint64_t(i * S::XROWS) * xrow, xvoff, sx + i * NT);
+            for (int i = 0; i < S::XL; ++i) split_dma16<XS>(xb + uint64_t(i * S::XROWS) * xrow, xvoff, sx + i * NT);
+        } else {
+#pragma unroll
+            for (int i = 0; i < S::WL; ++i) {
+                const int c = i * S::WROWS + tid / (BM / 2);
+                split_dma16<WS>(wb, wvoff + unsigned(min(c, last) - tid / (BM / 2)) * wrow, sw + i * NT);
+            }
+#pragma unroll
+            for (int i = 0; i < S::XL; ++i) {
+                const int c = i * S::XROWS + tid / (BN / 2);
+                split_dma16<XS>(xb, xvoff + unsigned(min(c, last) - tid / (BN / 2)) * xrow, sx + i * NT);
+            }
+        }
     };
 
     // One stage (16 channels = one reduction step).  Lane (quad, col) holds
@@ -271,34 +288,12 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
     constexpr int NB = PF + 1;
     constexpr int LPS = S::WL + S::XL;   // memory instructions per stage and thread
     // (a block of padding patches only has zero spectra: no stages)
-    const int nfull = t0 < nt ? cin / KC : 0, nstage = t0 < nt ? (cin + KC - 1) / KC : 0;
-    // The group's stage of iteration it (channel block s = it * KG + group)
-    // into its buffer; a partial last one through registers, its missing
-    // rows zero (their addresses clamped to the last row).
+    const int nstage = t0 < nt ? (cin + KC - 1) / KC : 0;
+    // The group's stage of iteration it (channel block it * KG + group).
+    auto buffer = [&](int it) __attribute__((always_inline)) { return lds + (NB == 2 ? it & 1 : it % NB) * S::STAGE; };
     auto load_stage = [&](int it) __attribute__((always_inline)) {
-        float2* const stage = lds + (NB == 2 ? it & 1 : it % NB) * S::STAGE;
         const int s = it * KG + group;
-        if (s < nfull) {
-            dma_stage(s * KC, stage);
-        } else if (s < nstage) {
-            const int k0 = s * KC, last = cin - 1 - k0;
-            const char* wsrc = reinterpret_cast<const char*>(ws + (size_t(f) * cin + k0) * coutp + co0) + (tid % (BM / 2)) * 16;
-            const char* xsrc = reinterpret_cast<const char*>(xs + spec_offset(k0, f, t0, nbins, ntp)) + (tid % (BN / 2)) * 16;
-            uint4* sw = reinterpret_cast<uint4*>(stage);
-            uint4* sx = reinterpret_cast<uint4*>(stage + S::WE);
-#pragma unroll
-            for (int i = 0; i < S::WL; ++i) {
-                const int c = i * S::WROWS + tid / (BM / 2);
-                const uint4 v = *reinterpret_cast<const uint4*>(wsrc + size_t(min(c, last)) * wrow);
-                sw[i * NT + tid] = c <= last ? v : make_uint4(0, 0, 0, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < S::XL; ++i) {
-                const int c = i * S::XROWS + tid / (BN / 2);
-                const uint4 v = *reinterpret_cast<const uint4*>(xsrc + size_t(min(c, last)) * xrow);
-                sx[i * NT + tid] = c <= last ? v : make_uint4(0, 0, 0, 0);
-            }
-        }
+        if (s < nstage) dma_stage(s, buffer(it));
     };
     auto run = [&](auto packed) __attribute__((always_inline)) {
         floatx4 accR[TM][TN], accI[TM][TN];
@@ -311,17 +306,27 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
 
 #pragma unroll
         for (int d = 0; d < PF; ++d) load_stage(d);
+        const int nit = (nstage + KG - 1) / KG;
         auto iterations = [&](int it, int end, auto neg) __attribute__((always_inline)) {
             for (; it < end; ++it) {
-                // this iteration's stage is whole once at most the loads of
-                // the group's whole stages issued after it remain; past the
-                // barrier every wave has also finished with the buffer of the
+                // this iteration's stage is there once at most the loads of
+                // the group's stages issued after it remain; past the barrier
+                // every wave has also finished with the buffer of the
                 // iteration before, which iteration it + PF then fills
                 const int s = it * KG + group;
-                const int later = s < nfull ? min(PF - 1, (nfull - 1 - s) / KG) : 0;
-                wait_stages<PF - 1, LPS>(later);
+                wait_stages<PF - 1, LPS>(s < nstage ? min(PF - 1, (nstage - 1 - s) / KG) : 0);
                 load_stage(it + PF);
-                const float2* cur = lds + (NB == 2 ? it & 1 : it % NB) * S::STAGE;
+                float2* const cur = buffer(it);
+                if (it == nit - 1 && cin % KC != 0) {
+                    // the partial block's missing filter rows (only its own
+                    // group's; the barrier is everyone's)
+                    const int last = cin - 1 - s * KC;
+#pragma unroll
+                    for (int i = 0; i < S::WL; ++i)
+                        if (i * S::WROWS + tid / (BM / 2) > last)
+                            reinterpret_cast<uint4*>(cur)[i * NT + tid] = make_uint4(0, 0, 0, 0);
+                    __syncthreads();
+                }
                 if (KG == 1 || s < nstage) multiply(cur, accR, accI, packed, neg);
             }
         };
@@ -338,7 +343,7 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
         // of the channels is therefore added to the negated sums, with the
         // patch operand's sign flipped, where they err the other way: about
         // a third of them, as the error of a step grows with the sum.
-        const int nit = (nstage + KG - 1) / KG, turn = nit - nit * 11 / 32;
+        const int turn = nit - nit * 11 / 32;
         iterations(0, turn, std::false_type{});
         negate();
         iterations(turn, nit, std::true_type{});
@@ -398,13 +403,16 @@ template <int BM, int BN, int TM, int TN, int PF, int KG = 1>
 static hipError_t launch_split_v(const fftsplit_plan_s& p, const float2* xs, const float2* ws, float2* ys,
                                  hipStream_t s, const LaunchEvents& ev) {
     using S = SplitShape<BM, BN, TM, TN>;
-    auto kern = contract_split_kernel<BM, BN, TM, TN, PF, KG, false, false>;
     constexpr int lds = KG * (PF + 1) * S::STAGE * 8;
     static_assert(lds <= 160 * 1024 && (KG - 1) * 2 * TM * TN * S::NT * 16 <= lds, "fits the LDS");
     if (p.coutp % BM != 0 || p.ntp % BN != 0) return hipErrorInvalidValue;
     const int nbco = p.coutp / BM, nbt = p.ntp / BN;
-    if (nbt <= 2) kern = contract_split_kernel<BM, BN, TM, TN, PF, KG, true, false>;
-    else if (nbco == 1) kern = contract_split_kernel<BM, BN, TM, TN, PF, KG, false, true>;
+    // Spectra that at most two workgroups (filter) or one (patches) read are
+    // streamed past the caches, as in contract_kernel.
+    auto kern = nbt <= 2 ? (nbco == 1 ? contract_split_kernel<BM, BN, TM, TN, PF, KG, true, true>
+                                      : contract_split_kernel<BM, BN, TM, TN, PF, KG, true, false>)
+                         : (nbco == 1 ? contract_split_kernel<BM, BN, TM, TN, PF, KG, false, true>
+                                      : contract_split_kernel<BM, BN, TM, TN, PF, KG, false, false>);
     const hipError_t attr = allow_dynamic_lds(kern, lds);
     if (attr != hipSuccess) return attr;
     const size_t nb = size_t(nbco) * nbt * p.bins;
@@ -419,9 +427,19 @@ hipError_t launch_contract_split(const fftsplit_plan_s& p, const float2* xs, con
         case kSplit256x64: return launch_split_v<256, 64, 4, 4, 1, 1>(p, xs, ws, ys, s, ev);
         case kSplit64x256: return launch_split_v<64, 256, 4, 4, 1, 1>(p, xs, ws, ys, s, ev);
         case kSplit128x64: return launch_split_v<128, 64, 4, 2, 1, 1>(p, xs, ws, ys, s, ev);
-        case kSplit64x64: return launch_split_v<64, 64, 2, 2, 2, 1>(p, xs, ws, ys, s, ev);
+        case kSplit64x64:
+            // two stages ahead (three workgroups on a compute unit) where
+            // there are more than four to load or the grid is no larger than
+            // that (the whole 1x64x224^2 layer: 28.4 us, one stage ahead
+            // 29.4); one ahead and four workgroups otherwise (the whole
+            // 11x119x182x55 -> 24 layer: 69.8, two ahead 71.8)
+            if (p.prob.cin > 4 * kChanBlock || size_t(p.coutp / 64) * (p.ntp / 64) * p.bins <= size_t(3) * p.cus)
+                return launch_split_v<64, 64, 2, 2, 2, 1>(p, xs, ws, ys, s, ev);
+            return launch_split_v<64, 64, 2, 2, 1, 1>(p, xs, ws, ys, s, ev);
         case kSplit64x64g2: return launch_split_v<64, 64, 2, 2, 1, 2>(p, xs, ws, ys, s, ev);
+        case kSplit128x32: return launch_split_v<128, 32, 2, 2, 1, 1>(p, xs, ws, ys, s, ev);
         case kSplit128x32g2: return launch_split_v<128, 32, 2, 2, 1, 2>(p, xs, ws, ys, s, ev);
+        case kSplit64x32g2: return launch_split_v<64, 32, 2, 2, 1, 2>(p, xs, ws, ys, s, ev);
         case kSplit64x32g4: return launch_split_v<64, 32, 2, 2, 1, 4>(p, xs, ws, ys, s, ev);
         case kSplitNone: break;
     }

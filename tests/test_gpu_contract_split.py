@@ -25,21 +25,25 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # (n, cin, h, w, cout, k), tile T, the tile the plan's rule gives
-    ((2, 97, 24, 24, 70, 3), 6, "64x32, four groups, a partial block"),
-    ((3, 80, 24, 24, 40, 3), 6, "64x32, four groups, five channel blocks"),
+    ((2, 97, 24, 24, 70, 3), 6, "64x32, two groups, a partial block"),
+    ((3, 80, 24, 24, 40, 3), 6, "64x32, two groups, five channel blocks"),
+    ((1, 270, 24, 24, 70, 3), 6, "64x32, four groups, a partial block"),
+    ((3, 256, 24, 24, 40, 3), 6, "64x32, four groups"),
     ((1, 3, 20, 40, 5, 3), 14, "64x64, one channel block, padding patches"),
-    ((2, 50, 24, 24, 40, 3), 14, "64x64, a partial block"),
+    ((20, 50, 56, 56, 40, 3), 14, "64x64, a partial block"),
     ((1, 1, 30, 30, 1, 3), 30, "64x64, one channel"),
-    ((5, 83, 56, 56, 192, 3), 14, "64x64, two groups, a partial block"),
+    ((5, 83, 56, 56, 192, 3), 14, "64x64, many blocks"),
+    ((3, 83, 56, 56, 64, 3), 14, "64x64, two groups, a partial block"),
     ((4, 96, 56, 40, 192, 3), 14, "64x64, two groups"),
-    ((2, 19, 28, 28, 128, 3), 14, "128x32, two groups"),
+    ((2, 19, 28, 28, 128, 3), 14, "128x32, a partial block"),
+    ((2, 53, 28, 28, 128, 3), 14, "128x32, two groups, a partial block"),
     ((5, 40, 42, 28, 256, 3), 14, "128x32, two groups, padding patches"),
-    ((4, 21, 100, 100, 128, 3), 30, "128x64"),
-    ((4, 31, 100, 100, 256, 3), 30, "256x64"),
-    ((8, 5, 110, 120, 128, 3), 30, "128x128"),
+    ((4, 37, 100, 100, 128, 3), 30, "128x64"),
+    ((4, 47, 100, 100, 256, 3), 30, "256x64"),
+    ((8, 35, 110, 120, 128, 3), 30, "128x128"),
     ((16, 34, 112, 100, 48, 3), 30, "64x256"),
     ((2, 18, 25, 25, 20, 5), 5, "64x64, odd transform size: no packed bins"),
-    ((2, 70, 25, 25, 20, 5), 5, "64x32, four groups, odd transform size"),
+    ((2, 70, 25, 25, 20, 5), 5, "64x32, two groups, odd transform size"),
 ]
 
 
