@@ -198,7 +198,8 @@ typedef struct {
  * Other environment variables read here (for experiments; the defaults are
  * the measured best): FFTSPLIT_CONTRACT_TILE (see contract_tile_m),
  * FFTSPLIT_CONTRACT_PREFETCH (see contract_prefetch),
- * FFTSPLIT_CONTRACT_SPLIT=0 (the contraction on the fp32 matrix instruction),
+ * FFTSPLIT_CONTRACT_SPLIT=0 / FFTSPLIT_DIRECT_SPLIT=0 (the contraction / the
+ * direct convolution on the fp32 matrix instruction),
  * FFTSPLIT_FORWARD_BAND=0 / FFTSPLIT_INVERSE_BAND=0 (general forward /
  * inverse kernels instead of the row-band ones), FFTSPLIT_FORWARD_SWEEP=1 / 0
  * (the row-band forward's workgroups run items a grid apart, or contiguous
@@ -273,8 +274,9 @@ fftsplit_status_t fftsplit_inverse(fftsplit_plan_t plan, const float* bias, floa
 
 /* The spatial convolution the paper compares the split method against
  * (Section 2, eq. 1 computed directly; Section 4): the same layer as the
- * plan's, as an implicit matrix product on the fp32 matrix cores, with the
- * plan's bias and ReLU flags.  The filters are first rearranged once per
+ * plan's, as an implicit matrix product in fp32 (on the fp32 matrix
+ * instruction, or on the bf16 one with every operand split exactly into three
+ * parts where that is faster: no less precise), with the plan's bias and ReLU flags.  The filters are first rearranged once per
  * layer:
  *   fftsplit_direct_transform_weights: w (device) [cout][cin][k][k] ->
  *     wd (device, info.direct_wspec_bytes) = [k*k][cin16][cout_padded],

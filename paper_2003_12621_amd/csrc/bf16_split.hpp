@@ -1,0 +1,39 @@
+// fp32 values as sums of three bf16 parts, for matrix products on the bf16
+// matrix instruction with fp32 results: v = h + m + l exactly (8 significand
+// bits each, rounded to nearest, so |m| <= 2^-9 |v| and |l| <= 2^-18 |v|).
+// The six part products down to 2^-18 (kSplitA, kSplitB: smallest first)
+// leave out less than 2^-26 of a product.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace fftsplit {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kSplitA[6] = {2, 0, 1, 1, 0, 0}, kSplitB[6] = {0, 2, 1, 0, 1, 0};
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+    const f32x2 v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+
+// Three dwords of bf16 pairs whose sum is (a, b).
+__device__ __forceinline__ void split3(float a, float b, unsigned (&p)[3]) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        p[q] = pack_bf16(a, b);
+        a -= __uint_as_float(p[q] << 16);
+        b -= __uint_as_float(p[q] & 0xffff0000u);
+    }
+}
+
+__device__ __forceinline__ floatx4 mfma_bf16(u32x4 a, u32x4 b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+}  // namespace fftsplit

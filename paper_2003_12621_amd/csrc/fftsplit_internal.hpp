@@ -29,6 +29,9 @@ struct fftsplit_plan_s {
     // tile of the bf16-split contraction kernel (k_contract_split.hip), or
     // kSplitNone where the fp32 one above runs
     int con_split;
+    // direct convolution on the bf16 instruction (k_direct.hip): log2 of the
+    // width of its 64-pixel blocks, or 0 where the fp32 kernel runs
+    int dir_ltw;
     // overlap-save band variant of the forward transform (band.hpp):
     // used if fwd_band; LDS row pitch, left zero columns, zero-row slot and
     // dynamic LDS bytes; fwd_sweep: items a grid apart instead of a

@@ -54,18 +54,13 @@
 // interleaved with the matrix instructions by the scheduler instead of two
 // waves overlapping, three stages ahead, and a priority for one of a compute
 // unit's two workgroups: no change.
+#include "bf16_split.hpp"
 #include "fftsplit_internal.hpp"
 #include "launch_util.hpp"
 
 #include <type_traits>
 
 namespace fftsplit {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // Waits until at most N vector memory instructions and no LDS read are
 // outstanding, then passes the workgroup's barrier.  One block, so that
@@ -105,11 +100,6 @@ __device__ __forceinline__ void split_dma16(uint64_t base, unsigned voff, const 
                      : "memory", "m0");
 }
 
-__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
-    const f32x2 v = {a, b};
-    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
-}
-
 // A 64-bit address that is the same in every lane, in scalar registers.
 // (readfirstlane returns a signed int: through unsigned, or the low word's
 // sign would overwrite the high word)
@@ -120,16 +110,6 @@ __device__ __forceinline__ uint64_t uniform_address(const void* p) {
     return uint64_t(lo) | uint64_t(hi) << 32;
 }
 
-// The filter operand: (re, im) -> three dwords of bf16 pairs whose sum is
-// (re, im).
-__device__ __forceinline__ void split_filter(float re, float im, unsigned (&a)[3]) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        a[q] = pack_bf16(re, im);
-        re -= __uint_as_float(a[q] << 16);
-        im -= __uint_as_float(a[q] & 0xffff0000u);
-    }
-}
 // The patch operand, for Re Y and for Im Y: the parts of (re, -im) and of
 // (im, re), or of (re, 0) and (0, im) in a slot of two real bins; NEG: of
 // their negatives.
@@ -242,8 +222,8 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
             for (int c = 0; c < 4; ++c) {
                 const float4 v = *reinterpret_cast<const float4*>(sw + c * BM + 32 * p);
                 unsigned q0[3], q1[3];
-                split_filter(v.x, v.y, q0);
-                split_filter(v.z, v.w, q1);
+                split3(v.x, v.y, q0);
+                split3(v.z, v.w, q1);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
                     a[q][2 * p][c] = q0[q];
@@ -270,16 +250,12 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
                     }
                 }
                 // smallest part products first
-                constexpr int PW[6] = {2, 0, 1, 1, 0, 0}, PX[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
                 for (int q = 0; q < 6; ++q)
 #pragma unroll
                     for (int i = 0; i < TM; ++i) {
-                        const bf16x8 w = __builtin_bit_cast(bf16x8, a[PW[q]][i]);
-                        accR[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            w, __builtin_bit_cast(bf16x8, br[PX[q]]), accR[i][j], 0, 0, 0);
-                        accI[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            w, __builtin_bit_cast(bf16x8, bi[PX[q]]), accI[i][j], 0, 0, 0);
+                        accR[i][j] = mfma_bf16(a[kSplitA[q]][i], br[kSplitB[q]], accR[i][j]);
+                        accI[i][j] = mfma_bf16(a[kSplitA[q]][i], bi[kSplitB[q]], accI[i][j]);
                     }
             }
         }

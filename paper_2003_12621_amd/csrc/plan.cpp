@@ -231,6 +231,39 @@ static void choose_contract_split(fftsplit_plan_s& p) {
     else p.con_split = kSplit64x64g2;
 }
 
+// The direct convolution's kernel.  The bf16 one takes 32 input channels a
+// step and blocks of 64 pixels (8x8, 4x16, 2x32 or 1x64, whichever covers the
+// image with the least waste) by 64 channels a wave, up to four waves sharing
+// the block's pixels: it is chosen where those roundings compute at most a
+// third more than the fp32 kernel's 16 channels and flattened pixels, the
+// filter is larger than 1x1 (8x128x30^2: 10 -> 21 us), the grid has four waves
+// for each compute unit (1568 of them, 4x64x112^2 -> 128: 97 -> 60 us; 600,
+// 30x54x35x27 -> 64: 39 -> 44) and its LDS leaves room for eight (K = 7 with
+// one wave a block, 5x123x89^2 -> 168: 1081 -> 1282).
+// FFTSPLIT_DIRECT_SPLIT=0 turns it off.
+static void choose_direct(fftsplit_plan_s& p) {
+    p.dir_ltw = 0;
+    if (const char* e = std::getenv("FFTSPLIT_DIRECT_SPLIT"))
+        if (*e == '0') return;
+    const size_t h = p.prob.h, w = p.prob.w;
+    int ltw = 3;
+    size_t cover = SIZE_MAX;
+    for (int l = 3; l <= 6; ++l) {
+        const size_t c = round_up(h, 64 >> l) * round_up(w, size_t(1) << l);
+        if (c < cover) {
+            cover = c;
+            ltw = l;
+        }
+    }
+    const size_t halo = p.prob.k / 2 * 2;
+    const size_t lds = 3 * 64 * ((64 >> ltw) + halo) * ((size_t(1) << ltw) + halo);
+    const size_t waves = size_t(p.prob.n) * (cover / 64) * (p.coutp / 64);
+    const size_t shared = p.coutp % 256 == 0 ? 4 : (p.coutp % 128 == 0 ? 2 : 1);
+    if (p.prob.k > 1 && lds * 8 <= size_t(160) * 1024 * shared && waves >= 1024 && waves <= size_t(INT_MAX) &&
+        3 * cover * round_up(p.prob.cin, 32) <= 4 * h * w * round_up(p.prob.cin, 16))
+        p.dir_ltw = ltw;
+}
+
 static fftsplit_status_t build_plan(const fftsplit_problem_t* prob, int device, const char* arch,
                                     fftsplit_plan_t* out) {
     if (!prob || !out) return fail(FFTSPLIT_ERROR_INVALID_VALUE, "problem and output pointers must be non-NULL");
@@ -436,6 +469,7 @@ static fftsplit_status_t build_plan(const fftsplit_problem_t* prob, int device, 
     }
 
     choose_contract_split(*plan);
+    choose_direct(*plan);
     choose_forward_band(*plan);
     choose_inverse_band(*plan);
     // The max-pool goes into the overlap-save inverse's store phase when no
