@@ -141,9 +141,11 @@ typedef struct {
      * per complex multiply-add.  It runs where the environment variable
      * FFTSPLIT_CONTRACT_TILE=[g3:|g4:]MxNxK (which overrides the choice),
      * FFTSPLIT_CONTRACT_PREFETCH or FFTSPLIT_CONTRACT_SPLIT=0 asks for it at
-     * plan time; otherwise the same product runs on the bf16 matrix
-     * instruction with every fp32 operand split exactly into three bf16
-     * parts, and is no less precise. */
+     * plan time, and on the shapes where it is the faster one (patches
+     * padded to 32 only, three or four whole channel blocks in a small grid);
+     * otherwise the same product runs on the bf16 matrix instruction with
+     * every fp32 operand split exactly into three bf16 parts, and is no less
+     * precise. */
     int contract_tile_m, contract_tile_n, contract_stage_k, contract_real_products;
     int spec_group;      /* G of the output-spectra layout */
     /* 1 if fftsplit_conv2d sums the input channels inside the inverse stage

@@ -63,7 +63,7 @@ namespace fftsplit {
 // that share the reduction).
 enum SplitTile {
     kSplitNone = 0, kSplit128x128, kSplit256x64, kSplit64x256, kSplit128x64, kSplit64x64, kSplit64x64g2,
-    kSplit128x32, kSplit128x32g2, kSplit64x32g2, kSplit64x32g4
+    kSplit64x32g2, kSplit64x32g4
 };
 
 // Granularity of the contraction's output tiles (patches x channels).

@@ -4,11 +4,12 @@
 // a batched complex matrix product -- the path's one dense contraction, and
 // the only place the matrix cores (MFMA) are used.
 //
-// This is the form on the fp32 matrix instruction.  Plans run
+// This is the form on the fp32 matrix instruction.  Most plans run
 // contract_split_kernel (k_contract_split.hip) instead, faster and closer to
-// the exact sums, unless FFTSPLIT_CONTRACT_TILE, FFTSPLIT_CONTRACT_PREFETCH
-// or FFTSPLIT_CONTRACT_SPLIT=0 asks for this one; the layouts, the grid order
-// and the cache policies are the same.
+// the exact sums; this one runs where it is as fast (choose_contract_split in
+// plan.cpp) or FFTSPLIT_CONTRACT_TILE, FFTSPLIT_CONTRACT_PREFETCH or
+// FFTSPLIT_CONTRACT_SPLIT=0 asks for it.  The layouts, the grid order and the
+// cache policies are the same.
 //
 // Each complex product is four real MFMA accumulations:
 //     Yr += Wr Xr - Wi Xi,   Yi += Wr Xi + Wi Xr.

@@ -1,19 +1,20 @@
-// Per-frequency-bin channel contraction on the bf16 matrix cores with fp32
-// results (the same product, layouts and grid order as contract_kernel in
+// Per-frequency-bin channel contraction on the bf16 matrix instruction with
+// fp32 results (the same product, layouts and grid order as contract_kernel in
 // k_contract.hip): for every stored bin f,
 //     Y[f][co][t] = sum_ci W[f][ci][co] * X[f][ci][t]        (complex).
 //
-// Each fp32 operand is split exactly into three bf16 parts, v = h + m + l
-// (8 significand bits each, rounded to nearest, so |m| <= 2^-9 |v| and
-// |l| <= 2^-18 |v|), and a product takes the six part products down to
-// 2^-18: l h', h l', m m', m h', h m', h h', accumulated in fp32.  What is
-// dropped (m l', l m', l l') is below 2^-26 of a product, under the fp32
-// rounding of one; and 16 products enter a matrix instruction before its sum
-// is rounded, against 2 in the fp32 instruction, so the sums are closer to
-// the exact ones than the fp32 kernel's (256 channels, normal operands: error
-// 2.4e-7 against 2.9e-7).  bf16 has fp32's exponent range, so no operand
-// needs scaling (operands below 2^-110 lose their smallest parts to
-// underflow).
+// Each fp32 operand is split exactly into three bf16 parts and a product
+// takes six part products (bf16_split.hpp), so a channel block's 16 products
+// are six matrix instructions.  Their rounding of the running sum is coarser
+// than a vector addition's: with that sum as their addend throughout, the
+// error against float64 was up to 30 % above the fp32 kernel's on a network's
+// activations (positive, correlated; below it on others).  In the last 3/8 of
+// the channels, where the sum is large, a block is therefore summed from zero
+// and then added in fp32.  Error over the layers of a VGG-16 stack at batch 4
+// and 32, against the fp32 kernel's: 0.67-0.96 of it; with every block from
+// zero 0.36-0.70, but 4-8 % slower.  bf16 has fp32's exponent range, so
+// no operand needs scaling (operands below 2^-110 lose their smallest parts
+// to underflow).
 //
 // A complex value (re, im) is one dword of two bf16, and the two sit side by
 // side along the matrix instruction's reduction (k = 2 ci, 2 ci + 1), so
@@ -31,29 +32,28 @@
 //
 // A workgroup tile is BM channels x BN patches of one bin, wave tiles of
 // 16 TM x 16 TN; channel blocks are loaded PF ahead straight into LDS as
-// fp32 and split after the LDS read.  At 64 x 64 a wave splits 8 values per
-// 48 matrix instructions: 400 vector instructions against 384 matrix
-// instructions of 16 cycles per channel block, which two waves per SIMD
-// overlap.  With KG > 1, KG wave groups take the channel blocks in turn and
-// add their sums through LDS: more waves on a compute unit that has one
-// workgroup (small grids, where a wave's chain of LDS read, split and product
-// is what takes the time).
+// fp32 and split after the LDS read.  At 64 x 64 a wave issues 400 vector
+// instructions of splits (and 128 additions where a block is summed from zero)
+// beside 384 matrix instructions of 16 cycles per channel block, which two
+// waves per SIMD overlap.  With KG > 1, KG wave groups take the channel blocks
+// in turn and add their sums through LDS: more waves on a compute unit that
+// has one workgroup (small grids, where a wave's chain of LDS read, split and
+// product is what takes the time).
 //
 // What bounds it (MI355X): the matrix cores, whose clock falls to 2.0 GHz
 // under it (2.4 under the fp32 kernel; a loop of the instruction alone
 // reaches 1745 TFLOP/s at 32x32x16 and 2040 at 16x16x32, hence that shape),
 // then the vector work and, with few patches, HBM.  Against the fp32 kernel,
 // whole launches in us (algorithmic rate at 8 flops per complex product):
-//     32x256x56^2, 512 patches            217 -> 164  (157 -> 209 TFLOP/s)
-//     32x512x28^2, 128 patches            217 -> 170
-//     32x128x112^2, 2048 patches          238 -> 178
-//     16x256x56^2 K=5, 64 patches         119 ->  97  (4.1 TB/s)
-//     32x64x224^2, 8192 patches           283 -> 245  (4.4 TB/s)
-//     1x512x28^2 at L = 8, 25 patches      34 ->  24
-// 32x32x16 instructions: 174 instead of 164 us on the first; the vector work
-// interleaved with the matrix instructions by the scheduler instead of two
-// waves overlapping, three stages ahead, and a priority for one of a compute
-// unit's two workgroups: no change.
+//     32x256x56^2, 512 patches            217 -> 171  (157 -> 201 TFLOP/s)
+//     32x512x28^2, 128 patches            217 -> 175
+//     32x128x112^2, 2048 patches          238 -> 177
+//     16x256x56^2 K=5, 64 patches         119 -> 100  (4.0 TB/s)
+//     32x64x224^2, 8192 patches           283 -> 240  (4.5 TB/s)
+//     1x512x28^2 at L = 8, 25 patches      34 ->  22
+// Tried without gain: the vector work interleaved with the matrix
+// instructions by the scheduler instead of two waves overlapping, three stages
+// ahead, and a priority for one of a compute unit's two workgroups.
 #include "bf16_split.hpp"
 #include "fftsplit_internal.hpp"
 #include "launch_util.hpp"
@@ -111,18 +111,16 @@ __device__ __forceinline__ uint64_t uniform_address(const void* p) {
 }
 
 // The patch operand, for Re Y and for Im Y: the parts of (re, -im) and of
-// (im, re), or of (re, 0) and (0, im) in a slot of two real bins; NEG: of
-// their negatives.
-template <bool PACKED, bool NEG>
+// (im, re), or of (re, 0) and (0, im) in a slot of two real bins.
+template <bool PACKED>
 __device__ __forceinline__ void split_patch(float re, float im, unsigned (&br)[3], unsigned (&bi)[3]) {
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        const unsigned v = NEG ? pack_bf16(-im, -re) : pack_bf16(im, re);
-        br[q] = PACKED ? v >> 16 : (NEG ? pack_bf16(-re, im) : pack_bf16(re, -im));
+        const unsigned v = pack_bf16(im, re);
+        br[q] = PACKED ? v >> 16 : pack_bf16(re, -im);
         bi[q] = PACKED ? v << 16 : v;
-        const float vi = __uint_as_float(v << 16), vr = __uint_as_float(v & 0xffff0000u);
-        im = NEG ? im + vi : im - vi;
-        re = NEG ? re + vr : re - vr;
+        im -= __uint_as_float(v << 16);
+        re -= __uint_as_float(v & 0xffff0000u);
     }
 }
 
@@ -212,7 +210,7 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
     // wave's tile, one 16-byte LDS read per channel and pair; the filter
     // parts of the whole tile stay in registers, the patch parts are made a
     // column block at a time.
-    auto multiply = [&](const float2* stage, floatx4 (&accR)[TM][TN], floatx4 (&accI)[TM][TN], auto packed, auto neg) __attribute__((always_inline)) {
+    auto multiply = [&](const float2* stage, floatx4 (&accR)[TM][TN], floatx4 (&accI)[TM][TN], auto packed, auto fresh) __attribute__((always_inline)) {
         const float2* sw = stage + (4 * quad) * BM + wm * (16 * TM) + 2 * col;
         const float2* sx = stage + S::WE + (4 * quad) * BN + wn * (16 * TN) + 2 * col;
         u32x4 a[3][TM];
@@ -242,21 +240,29 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     unsigned qr[3], qi[3];
-                    split_patch<decltype(packed)::value, decltype(neg)::value>(e ? v[c].z : v[c].x, e ? v[c].w : v[c].y, qr, qi);
+                    split_patch<decltype(packed)::value>(e ? v[c].z : v[c].x, e ? v[c].w : v[c].y, qr, qi);
 #pragma unroll
                     for (int q = 0; q < 3; ++q) {
                         br[q][c] = qr[q];
                         bi[q][c] = qi[q];
                     }
                 }
-                // smallest part products first
+                // Smallest part products first; `fresh`: the block's sum from
+                // zero, then one fp32 addition.
+                auto add = [&](const u32x4 (&b)[3], floatx4 (&acc)[TM][TN]) __attribute__((always_inline)) {
+                    constexpr bool F = decltype(fresh)::value;
+                    floatx4 t[TM];
 #pragma unroll
-                for (int q = 0; q < 6; ++q)
+                    for (int i = 0; i < TM; ++i) t[i] = F ? floatx4{0.f, 0.f, 0.f, 0.f} : acc[i][j];
 #pragma unroll
-                    for (int i = 0; i < TM; ++i) {
-                        accR[i][j] = mfma_bf16(a[kSplitA[q]][i], br[kSplitB[q]], accR[i][j]);
-                        accI[i][j] = mfma_bf16(a[kSplitA[q]][i], bi[kSplitB[q]], accI[i][j]);
-                    }
+                    for (int q = 0; q < 6; ++q)
+#pragma unroll
+                        for (int i = 0; i < TM; ++i) t[i] = mfma_bf16(a[kSplitA[q]][i], b[kSplitB[q]], t[i]);
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) acc[i][j] = F ? acc[i][j] + t[i] : t[i];
+                };
+                add(br, accR);
+                add(bi, accI);
             }
         }
     };
@@ -283,7 +289,7 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
 #pragma unroll
         for (int d = 0; d < PF; ++d) load_stage(d);
         const int nit = (nstage + KG - 1) / KG;
-        auto iterations = [&](int it, int end, auto neg) __attribute__((always_inline)) {
+        auto iterations = [&](int it, int end, auto fresh) __attribute__((always_inline)) {
             for (; it < end; ++it) {
                 // this iteration's stage is there once at most the loads of
                 // the group's stages issued after it remain; past the barrier
@@ -303,27 +309,16 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
                             reinterpret_cast<uint4*>(cur)[i * NT + tid] = make_uint4(0, 0, 0, 0);
                     __syncthreads();
                 }
-                if (KG == 1 || s < nstage) multiply(cur, accR, accI, packed, neg);
+                if (KG == 1 || s < nstage) multiply(cur, accR, accI, packed, fresh);
             }
         };
-        auto negate = [&]() __attribute__((always_inline)) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    accR[i][j] = -accR[i][j];
-                    accI[i][j] = -accI[i][j];
-                }
-        };
-        // The matrix unit's sums err towards minus infinity.  The last part
-        // of the channels is therefore added to the negated sums, with the
-        // patch operand's sign flipped, where they err the other way: about
-        // a third of them, as the error of a step grows with the sum.
-        const int turn = nit - nit * 11 / 32;
-        iterations(0, turn, std::false_type{});
-        negate();
-        iterations(turn, nit, std::true_type{});
-        negate();
+        // The first 5/8 of the channels are added by the matrix instructions
+        // themselves, the rest from zero (see above): a step's error grows
+        // with the sum, so that part holds about half of the squared error.
+        // Wave groups' sums are short enough without.
+        const int direct = KG > 1 ? nit : nit * 5 / 8;
+        iterations(0, direct, std::false_type{});
+        if constexpr (KG == 1) iterations(direct, nit, std::true_type{});
         if constexpr (KG > 1) {
             // the groups' partial sums, through LDS to the first group
             constexpr int NA = 2 * TM * TN;
@@ -413,8 +408,6 @@ hipError_t launch_contract_split(const fftsplit_plan_s& p, const float2* xs, con
                 return launch_split_v<64, 64, 2, 2, 2, 1>(p, xs, ws, ys, s, ev);
             return launch_split_v<64, 64, 2, 2, 1, 1>(p, xs, ws, ys, s, ev);
         case kSplit64x64g2: return launch_split_v<64, 64, 2, 2, 1, 2>(p, xs, ws, ys, s, ev);
-        case kSplit128x32: return launch_split_v<128, 32, 2, 2, 1, 1>(p, xs, ws, ys, s, ev);
-        case kSplit128x32g2: return launch_split_v<128, 32, 2, 2, 1, 2>(p, xs, ws, ys, s, ev);
         case kSplit64x32g2: return launch_split_v<64, 32, 2, 2, 1, 2>(p, xs, ws, ys, s, ev);
         case kSplit64x32g4: return launch_split_v<64, 32, 2, 2, 1, 4>(p, xs, ws, ys, s, ev);
         case kSplitNone: break;

@@ -180,8 +180,6 @@ static const char* split_tile_name(int tile) {
         case kSplit128x64: return "split 128x64";
         case kSplit64x64: return "split 64x64";
         case kSplit64x64g2: return "split 64x64/2";
-        case kSplit128x32: return "split 128x32";
-        case kSplit128x32g2: return "split 128x32/2";
         case kSplit64x32g2: return "split 64x32/2";
         case kSplit64x32g4: return "split 64x32/4";
     }
@@ -192,22 +190,26 @@ static const char* split_tile_name(int tile) {
 // gives (two of the large ones fill a compute unit, so 512 the chip).  A
 // wave's tile of 64 x 64 needs the fewest splits and LDS reads per product,
 // so the largest tile that still fills the chip is taken; the contraction of
-// the layers named, in us: 16x256x56^2 K=5 (one patch block) 256x64 97,
-// 128x64 103, 64x64 112; 8x128x112^2 128x128 48, 128x64 52, 64x64 55;
-// 32x64x224^2 64x256 243, 64x64 265.  With at most two channel blocks there
-// is little to multiply and the outputs' stores dominate: 64x64, five
-// workgroups on a compute unit (the whole 18x3x254x255 -> 18 layer: 148 us,
-// 64x256 160).  Where no large tile fills the chip (4x256x56^2: 256x64 46,
-// 64x64 30; 1x64x224^2: 64x256 17, 64x64 12), 64x64 tiles; where these do not
-// either and there are more than four channel blocks, in two wave groups that
-// take the blocks in turn (1x256x28^2 at L = 8: 16.9, one group 19.5; with
-// 512 workgroups the groups cost more than they give, 4x256x56^2: 31.7, one
-// group 29.8); and where even half of those
+// the layers named, in us: 16x256x56^2 K=5 (one patch block) 256x64 104,
+// 128x64 108, 64x64 117; 8x128x112^2 128x128 55, 64x64 57; 32x64x224^2
+// 64x256 244, 64x64 257.  With at most two channel blocks there is little to
+// multiply and the outputs' stores dominate: 64x64, four workgroups on a
+// compute unit.  Where no large tile fills the chip (4x256x56^2: 256x64 53,
+// 64x64 in two groups 33; 1x64x224^2: 64x256 19, 64x64 13), 64x64 tiles; up
+// to two workgroups a compute unit and with more than four channel blocks, in
+// two wave groups that take the blocks in turn (1x256x28^2 at L = 8: 18.0,
+// one group 21.3; 1x128x112^2: 11.6 and 12.8); and where even half of those
 // patches leaves compute units idle, 64x32 in four groups (1x512x28^2 at
-// L = 8, 25 patches: 24, 64x64 in two groups 28), or in two with fewer than
+// L = 8, 25 patches: 24, 64x64 in two groups 31), or in two with fewer than
 // 16 blocks (the whole 10x64x12^2 K=5 -> 8 layer: 14.7, 64x64 16.3; 1x99x12^2
-// K=1 -> 484: 21.9, four groups 24.3).  Patches padded to 32 only: 128x32 in
-// two groups (4x512x28^2: 59, one group 63), one with at most two blocks.
+// K=1 -> 484: 21.9, four groups 24.3).
+// Patches padded to 32 only stay on the fp32 kernel's 128x32 tiles: there the
+// filter spectra's stream is what takes the time (300 MB in 65 us on
+// 32x512x14^2), and split 128x32 tiles, 63-68 us, made the whole layer 80-89 us
+// against 81-84 on different boards.  Three or four whole channel blocks in a grid of at most three workgroups a
+// compute unit stay on the fp32 kernel, whose whole sum is loaded at once and
+// whose waves have the shorter chain (the whole 1x64x224^2 layer: 28.8 us,
+// 64x64 split 29.3).
 // An explicit FFTSPLIT_CONTRACT_TILE or _PREFETCH, or
 // FFTSPLIT_CONTRACT_SPLIT=0, selects the fp32 kernel instead.
 static void choose_contract_split(fftsplit_plan_s& p) {
@@ -220,14 +222,15 @@ static void choose_contract_split(fftsplit_plan_s& p) {
     };
     constexpr size_t kFull = 512;
     const size_t half_blocks = size_t(p.coutp / 64) * size_t((p.nt + 31) / 32) * size_t(p.bins);
-    if (p.ntp % 64 != 0) p.con_split = p.prob.cin <= 2 * kChanBlock ? kSplit128x32 : kSplit128x32g2;
-    else if (p.prob.cin <= 2 * kChanBlock) p.con_split = kSplit64x64;
+    if (p.ntp % 64 != 0) return;
+    if (p.prob.cin <= 2 * kChanBlock) p.con_split = kSplit64x64;
     else if (blocks(128, 128) >= kFull) p.con_split = kSplit128x128;
     else if (blocks(256, 64) >= kFull) p.con_split = kSplit256x64;
     else if (blocks(64, 256) >= kFull) p.con_split = kSplit64x256;
     else if (blocks(128, 64) >= kFull) p.con_split = kSplit128x64;
     else if (half_blocks <= kFull / 2) p.con_split = p.prob.cin >= 16 * kChanBlock ? kSplit64x32g4 : kSplit64x32g2;
-    else if (p.prob.cin <= 4 * kChanBlock || blocks(64, 64) >= kFull) p.con_split = kSplit64x64;
+    else if (p.prob.cin <= 4 * kChanBlock && p.prob.cin % kChanBlock == 0 && blocks(64, 64) <= size_t(3) * p.cus) return;
+    else if (p.prob.cin <= 4 * kChanBlock || blocks(64, 64) > kFull) p.con_split = kSplit64x64;
     else p.con_split = kSplit64x64g2;
 }
 

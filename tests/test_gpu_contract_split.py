@@ -6,12 +6,11 @@ that leave whole blocks of padding, and the two slots of real bins, against
 the float64 channel sum of the GPU's own spectra.
 
 Tolerance.  An operand is its three bf16 parts exactly, and what six of the
-nine part products leave out is below 2^-26 of a product.  The rest is fp32
-accumulation of 2 cin real products: 6 matrix instructions per 16 channels,
-each rounding its running sum, and at most 3 further additions of partial
-sums.  With each rounding below 2^-24 of the sum of absolute products (2^-23
-for an instruction that rounds inside as well),
-    |Y - ref| <= (6 ceil(cin / 16) + 3) 2^-23 (|W| |X|).
+nine part products leave out is below 2^-26 of a product.  Each block of 16
+channels is summed by six matrix instructions and added in fp32, and at most 3
+further additions join the wave groups' sums.  With each of those roundings
+below 2^-23 of the sum of absolute products so far,
+    |Y - ref| <= (7 ceil(cin / 16) + 3) 2^-23 (|W| |X|).
 """
 import numpy as np
 import pytest
@@ -34,10 +33,7 @@ CASES = [
     ((1, 1, 30, 30, 1, 3), 30, "64x64, one channel"),
     ((5, 83, 56, 56, 192, 3), 14, "64x64, many blocks"),
     ((3, 83, 56, 56, 64, 3), 14, "64x64, two groups, a partial block"),
-    ((4, 96, 56, 40, 192, 3), 14, "64x64, two groups"),
-    ((2, 19, 28, 28, 128, 3), 14, "128x32, a partial block"),
-    ((2, 53, 28, 28, 128, 3), 14, "128x32, two groups, a partial block"),
-    ((5, 40, 42, 28, 256, 3), 14, "128x32, two groups, padding patches"),
+    ((4, 96, 56, 40, 192, 3), 14, "64x64, two groups, even blocks"),
     ((4, 37, 100, 100, 128, 3), 30, "128x64"),
     ((4, 47, 100, 100, 256, 3), 30, "256x64"),
     ((8, 35, 110, 120, 128, 3), 30, "128x128"),
@@ -47,13 +43,14 @@ CASES = [
 ]
 
 
-def _spectra(shape, tile, scale=1.0):
+def _spectra(shape, tile, scale=1.0, mean=0.0):
     x, w = small_layer(*shape, seed=sum(shape))
+    x = (x + np.float32(mean)) * np.float32(scale)
     plan = fs.Plan(*shape, tile=tile, mode="oaa" if tile == shape[5] else "os")
     ws = plan.new_workspace()
     ws.fill_(0xFF)   # NaN wherever nothing is written
     wspec = plan.transform_weights(torch.from_numpy(w).cuda())
-    plan.forward(torch.from_numpy(np.ascontiguousarray(x * np.float32(scale))).cuda(), ws)
+    plan.forward(torch.from_numpy(np.ascontiguousarray(x)).cuda(), ws)
     plan.contract(wspec, ws)
     nt = plan.info.tiles
     X, W = plan.xspec_view(ws)[:, :, :nt], plan.wspec_view(wspec)
@@ -74,7 +71,7 @@ def test_against_float64(shape, tile, what):
     X, W, got, plan = _spectra(shape, tile)
     ref, mag = _channel_sum(X, W, plan.nfft % 2 == 0)
     nt = plan.info.tiles
-    bound = (6 * -(-shape[1] // 16) + 3) * 2.0 ** -23
+    bound = (7 * -(-shape[1] // 16) + 3) * 2.0 ** -23
     err = (got[:, :, :nt].to(torch.complex128) - ref).abs()
     assert bool((err <= bound * mag).all()), float((err / mag.clamp_min(1e-300)).max()) / bound
     # padded output channels and padding patches are zero spectra
@@ -82,18 +79,19 @@ def test_against_float64(shape, tile, what):
 
 
 @pytest.mark.parametrize("shape,tile", [((4, 256, 56, 56, 256, 3), 14), ((16, 64, 56, 56, 256, 5), 28),
-                                        ((2, 512, 14, 14, 128, 3), 6)])
-@pytest.mark.parametrize("scale", [1.0, 2.0 ** -60, 2.0 ** 60])
-def test_no_less_precise_than_fp32(shape, tile, scale, monkeypatch):
+                                        ((2, 512, 14, 14, 128, 3), 6), ((4, 512, 28, 28, 512, 3), 6)])
+@pytest.mark.parametrize("scale,mean", [(1.0, 0.0), (2.0 ** -60, 0.0), (2.0 ** 60, 0.0), (1.0, 3.0)])
+def test_no_less_precise_than_fp32(shape, tile, scale, mean, monkeypatch):
     """Its error against float64 is no larger than the fp32 matrix
-    instruction's on the same spectra, at any scale of the input."""
+    instruction's on the same spectra, at any scale of the input, and where
+    every pixel is positive and the sums lean one way."""
     def error():
-        X, W, got, plan = _spectra(shape, tile, scale)
+        X, W, got, plan = _spectra(shape, tile, scale, mean)
         ref, _ = _channel_sum(X, W, True)
         d = got[:, :, :plan.info.tiles].to(torch.complex128) - ref
         return float((d / scale).abs().pow(2).sum().sqrt() / (ref / scale).abs().pow(2).sum().sqrt())
     split = error()
     monkeypatch.setenv("FFTSPLIT_CONTRACT_SPLIT", "0")
     fp32 = error()
-    print(f"[case] {shape} scale={scale:g}: split {split:.3e} fp32 {fp32:.3e}", flush=True)
+    print(f"[case] {shape} scale={scale:g} mean={mean}: split {split:.3e} fp32 {fp32:.3e}", flush=True)
     assert split <= fp32
