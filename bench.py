@@ -39,6 +39,9 @@ import numpy as np  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
 FP32_MFMA_PEAK_TFLOPS = 157.3  # MI355X dense fp32 matrix, TFLOP/s
+# fp32 products on the bf16 matrix instruction, six part products each
+# (2.5 PFLOP/s dense bf16): the contraction's default kernel
+SPLIT_MFMA_PEAK_TFLOPS = 2500.0 / 6
 
 DEFAULT_CONFIG = "c4_56x256_k5"
 DEFAULT_TILE = 28
@@ -362,8 +365,16 @@ def matrix_ceiling(run, con_ms, steps=20):
             "executed_flops": executed,
             "probe_frac_of_peak": round(executed / (probe_us * 1e-6) / 1e12 / FP32_MFMA_PEAK_TFLOPS, 4),
             "contract_vs_probe": round(probe_us / (con_ms * 1e3), 4),
-            "note": "fftsplit_probe_matrix: the contraction's grid, occupancy and matrix operations per wave with "
-                    "no memory traffic; contract_vs_probe = probe time / contraction time (warm)"}
+            "note": "fftsplit_probe_matrix: the fp32 contraction kernel's grid, occupancy and matrix operations per "
+                    "wave with no memory traffic; contract_vs_probe = probe time / contraction time (warm; above 1 "
+                    "where the contraction runs on the bf16 instruction)"}
+
+
+def on_split_kernel():
+    """Whether no environment variable keeps the contraction on the fp32
+    matrix instruction (the headline layer's plan then runs the bf16 one)."""
+    return not (os.environ.get("FFTSPLIT_CONTRACT_TILE") or "FFTSPLIT_CONTRACT_PREFETCH" in os.environ
+                or os.environ.get("FFTSPLIT_CONTRACT_SPLIT", "").startswith("0"))
 
 
 def stage_record(counts, fwd, con, inv):
@@ -681,6 +692,9 @@ def main():
     wtag = f"{args.config}_T{tile}_{args.mode}"
     stages["forward"]["traffic"] = load_traffic("forward", wtag)
     stages["inverse"]["traffic"] = load_traffic("inverse", wtag)
+    split = on_split_kernel()
+    con_peak = SPLIT_MFMA_PEAK_TFLOPS if split else FP32_MFMA_PEAK_TFLOPS
+    products = 4 if split else info.contract_real_products
     out = {
         "metric": "effective direct-conv GFLOP/s",
         "value": round(value, 1),
@@ -698,18 +712,23 @@ def main():
                                f"cout={layer.cout} k={layer.k} stride1 same",
                    "tile": info.tile, "nfft": info.nfft, "mode": args.mode, "tiles": info.tiles,
                    "bins": info.bins,
-                   "contract_variant": f"{info.contract_tile_m}x{info.contract_tile_n}x{info.contract_stage_k}"
+                   "contract_variant": "bf16 split, 6 part products" if split else
+                                       f"{info.contract_tile_m}x{info.contract_tile_n}x{info.contract_stage_k}"
                                        f"/{info.contract_real_products}M/prefetch{info.contract_prefetch}"},
         "images_per_s": round(layer.n / (ms_per_step * 1e-3), 1),
         "settle_s": round(settle_s, 3),
         "settle_steps": settle_n,
         "roofline": {"bound": "mfma", "kernel": "contract (per-bin complex Cin->Cout product)",
-                     "achieved": con_tfs, "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": round(con_tfs / FP32_MFMA_PEAK_TFLOPS, 4), "traffic": load_traffic("contract", wtag),
+                     "achieved": con_tfs, "peak": round(con_peak, 1), "unit": "TFLOP/s",
+                     "frac": round(con_tfs / con_peak, 4), "traffic": load_traffic("contract", wtag),
                      "flops_per_complex_mac": 8,
-                     "mfma_real_products_per_complex_mac": info.contract_real_products,
-                     "mfma_executed_frac": round(con_tfs * info.contract_real_products / 4
-                                                 / FP32_MFMA_PEAK_TFLOPS, 4)},
+                     "mfma_real_products_per_complex_mac": products,
+                     "mfma_executed_frac": round(con_tfs * products / 4 / con_peak, 4),
+                     "frac_of_fp32_mfma_peak": round(con_tfs / FP32_MFMA_PEAK_TFLOPS, 4),
+                     "note": "peak: fp32 products on the bf16 matrix instruction, six part products each "
+                             "(2500 / 6 TFLOP/s); frac_mfma in `stages` and `workloads` is of the fp32 matrix "
+                             "peak (157.3 TFLOP/s), which those kernels can exceed" if split else
+                             "peak: the fp32 matrix instruction"},
         "stages": stages,
         "stages_cold": None if cold is None else {
             "forward": {"ms": round(cold[0], 4), "frac_hbm": round(counts["forward_bytes"] / (cold[0] * 1e-3) / 1e9

@@ -66,7 +66,8 @@ def build(verbose: bool = False) -> str:
 KERNEL_SOURCES = {
     "forward": ["k_forward.hip", "band.hpp", "fft_regs.hpp", "twiddles.inc", "launch_util.hpp",
                 "fftsplit_internal.hpp"],
-    "contract": ["k_contract.hip", "k_contract_split.hip", "launch_util.hpp", "fftsplit_internal.hpp"],
+    "contract": ["k_contract.hip", "k_contract_split.hip", "bf16_split.hpp", "launch_util.hpp",
+                 "fftsplit_internal.hpp"],
     "inverse": ["k_inverse.hip", "band.hpp", "fft_regs.hpp", "twiddles.inc", "launch_util.hpp",
                 "fftsplit_internal.hpp"],
 }
