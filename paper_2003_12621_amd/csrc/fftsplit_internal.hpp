@@ -122,6 +122,17 @@ __host__ __device__ inline size_t yspec_offset(int c, int f, int t, int bins, in
     return ((size_t(c) * ngroups + t / G) * bins + f) * size_t(G) + t % G;
 }
 
+// Overlap-add aux buffer: of a patch's L x L result the entries outside the
+// cs x cs core (cs = T - 2P) are kept, packed: the L - cs last rows whole,
+// then the L - cs last entries of each core row.  With the whole L x L square
+// kept, a core row's few entries took a 64-byte line of their own: inverse +
+// seam pass 38.4 + 30.0 us on 8x128x112^2 K = 3 (T = 14, 112 of 256 entries),
+// packed 30.9 + 26.0 us; T = 30 36.4 + 25.6 and 36.2 + 14.2 us.
+__host__ __device__ constexpr int seam_entries(int L, int cs) { return L * L - cs * cs; }
+__host__ __device__ constexpr int seam_entry(int m, int q, int L, int cs) {
+    return m >= cs ? (m - cs) * L + q : (L - cs) * L + m * (L - cs) + (q - cs);
+}
+
 // Stored frequency bins of an L x L real transform: L*L/2 (layout in
 // fftsplit.h).  Bins with k2 in [1, L/2-1] (all k1) are stored as they are;
 // of the columns k2 = 0 and k2 = L/2, which are Hermitian in k1, the

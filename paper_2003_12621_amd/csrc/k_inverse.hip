@@ -23,7 +23,7 @@
 //      region around its tile.  Entries with p, q < T-2P (the "core") have
 //      no other contributor and are written directly with bias and ReLU;
 //      the rest (seams, 2P wide, shared by 2 or 4 neighbouring patches) go to
-//      a per-patch L x L slot of the aux buffer, and seam_kernel then sums
+//      the patch's slot of the aux buffer (seam_entry), and seam_kernel then sums
 //      the 1-4 contributions of every seam pixel in a fixed order (no
 //      atomics, deterministic) and applies bias and ReLU.
 // The inverse's 1/L^2 is already folded into the filter spectra.
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(TG * (L / 2)) void inverse_kernel(const float2* __r
                     buf_store_f32(v, ry_out, vo, 0);
                 }
             } else if (t0 + u < nt) {
-                float* slot = aux + (co * ntp + t0 + u) * (L * L);
+                float* slot = aux + (co * ntp + t0 + u) * seam_entries(L, cs);
 #pragma unroll
                 for (int mb = 0; mb < L; mb += S::MS) {
                     const int m = mb + ms;
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(TG * (L / 2)) void inverse_kernel(const float2* __r
                             y[d + m * w + q] = v;
                         }
                     } else {
-                        slot[m * L + q] = zv;
+                        slot[seam_entry(m, q, L, cs)] = zv;
                     }
                 }
             }
@@ -260,8 +260,9 @@ __global__ __launch_bounds__(256) void seam_kernel(const float* __restrict__ aux
     const int plane = blockIdx.x / bpp;
     const int blk = blockIdx.x - plane * bpp;
     const int img = plane / cout, co = plane % cout;
-    const int P2 = 2 * P, LL = L * L;
-    const BufRsrc rin = make_rsrc(aux + (size_t(co) * ntp + size_t(img) * th * tw) * LL, unsigned(th * tw * LL * 4));
+    const int P2 = 2 * P, core = T - P2, entries = seam_entries(L, core);
+    const BufRsrc rin = make_rsrc(aux + (size_t(co) * ntp + size_t(img) * th * tw) * entries,
+                                  unsigned(th * tw * entries * 4));
     const int n_row = nsr * w, n_all = n_row + (h - nsr) * nsc;
     float v[kSeamPix][4];
     int out[kSeamPix];
@@ -298,7 +299,8 @@ __global__ __launch_bounds__(256) void seam_kernel(const float* __restrict__ aux
                 int qq = c - b * T - P;
                 if (qq < 0) qq += L;
                 const bool ok = ok_a && (!db || seam_c) && b >= 0 && b < tw;
-                const unsigned off = ok ? unsigned(((a * tw + b) * L + p) * L + qq) * 4u : kOutOfRange;
+                const unsigned off =
+                    ok ? unsigned((a * tw + b) * entries + seam_entry(p, qq, L, core)) * 4u : kOutOfRange;
                 v[i][2 * (1 - da) + (1 - db)] = buf_load_f32(rin, off, 0);
             }
         }

@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void oaa_inverse_kernel(const float2* __restri
     const int rest = t / tw;
     const int a = rest % th;
     const int img = rest / th;
-    float* slot = aux + (size_t(co) * ntp + t) * (L * L);
+    float* slot = aux + (size_t(co) * ntp + t) * seam_entries(L, 1);
     float o[L][L];
     oaa_inverse_patch<L>(Y, o);
 #pragma unroll
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(256) void oaa_inverse_kernel(const float2* __restri
                     y[((size_t(img) * cout + co) * h + r) * w + cc] = v;
                 }
             } else {
-                slot[m * L + q] = o[m][q];
+                slot[seam_entry(m, q, L, 1)] = o[m][q];
             }
         }
 }

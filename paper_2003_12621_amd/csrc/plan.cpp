@@ -396,7 +396,8 @@ static fftsplit_status_t build_plan(const fftsplit_problem_t* prob, int device, 
     plan->yspec_off = round_up(xs, 256);
     plan->yspec_bytes = ys;
     plan->aux_off = round_up(plan->yspec_off + ys, 256);
-    // Overlap-add keeps each patch's L x L inverse result for the seam pass.
+    // Overlap-add keeps the seam entries of each patch's L x L inverse result
+    // (at most L x L of them) for the seam pass.
     plan->aux_bytes = oaa ? size_t(p.cout) * size_t(g.ntp) * size_t(g.L) * size_t(g.L) * 4 : 0;
     plan->ws_bytes = plan->aux_off + plan->aux_bytes;
 
