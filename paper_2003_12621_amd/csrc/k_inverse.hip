@@ -251,52 +251,71 @@ __global__ __launch_bounds__(TG * (L / 2)) void inverse_kernel(const float2* __r
 // contribution reads an out-of-range offset of a descriptor over the
 // plane's patch results, which returns 0, so every pixel sums four terms in
 // the fixed order (adding +0 leaves a sum unchanged).
+//
+// Bound: partly written lines at small T (a column seam's 2P pixels of a row
+// are a few bytes of a line that inverse_kernel wrote around), index
+// arithmetic at large T.  With the compiler's integer division (about 30
+// vector instructions, eight of them a pixel) the pass took 26.0 us on
+// 8x128x112^2 K = 3 T = 14 and 14.2 at T = 30; with three divisions a pixel,
+// each a multiplication by a reciprocal from the host (the other quotients
+// follow from how the pixels are enumerated), 24.8 and 10.8.  Whole calls:
+// that layer at T = 30 150.7 -> 146.7 us, 8x64x112^2 K = 5 T = 28 74.6 ->
+// 71.7, 3x61x57x75 K = 7 T = 10 45.0 -> 42.5, 16x64x224^2 K = 3 T = 30 503 -> 501.
 constexpr int kSeamPix = 4;
+
+struct SeamGeometry {
+    int nsr, nsc, bpp;                 // seam rows and columns, blocks per plane
+    FastDiv w, nsc_div, T, P2, core;   // the divisors of the enumeration
+};
 
 __global__ __launch_bounds__(256) void seam_kernel(const float* __restrict__ aux, const float* __restrict__ bias,
                                                    float* __restrict__ y, int cout, int h, int w, int T, int P, int L,
-                                                   int th, int tw, int ntp, int relu, int nsr, int nsc, int bpp) {
+                                                   int th, int tw, int ntp, int relu, SeamGeometry g) {
     // blocks run plane-major, bpp blocks per plane
-    const int plane = blockIdx.x / bpp;
-    const int blk = blockIdx.x - plane * bpp;
+    const int plane = blockIdx.x / g.bpp;
+    const int blk = blockIdx.x - plane * g.bpp;
     const int img = plane / cout, co = plane % cout;
     const int P2 = 2 * P, core = T - P2, entries = seam_entries(L, core);
     const BufRsrc rin = make_rsrc(aux + (size_t(co) * ntp + size_t(img) * th * tw) * entries,
                                   unsigned(th * tw * entries * 4));
-    const int n_row = nsr * w, n_all = n_row + (h - nsr) * nsc;
+    const int n_row = g.nsr * w, n_all = n_row + (h - g.nsr) * g.nsc;
     float v[kSeamPix][4];
     int out[kSeamPix];
 #pragma unroll
     for (int i = 0; i < kSeamPix; ++i) {
+        // the pixel is (a0 T - P + pr, b0 T - P + pc), 0 <= pr, pc < T
         const int idx = (blk * kSeamPix + i) * 256 + threadIdx.x;
-        int r = 0, c = 0;
+        int a0 = 0, b0 = 0, pr = P, pc = P;
         bool seam_r = true;
         if (idx < n_row) {
-            const int k = idx / w;
-            c = idx - k * w;
-            r = ((k + P) / P2) * T - P + (k + P) % P2;
+            const int k = g.w.quotient(idx);
+            a0 = g.P2.quotient(k + P);
+            pr = k + P - a0 * P2;
+            const int c = idx - k * w + P;
+            b0 = g.T.quotient(c);
+            pc = c - b0 * T;
         } else if (idx < n_all) {
             const int j = idx - n_row;
-            const int k = j / nsc, sc = j - k * nsc;
-            const int cs = T - P2;
-            r = (k / cs) * T + P + k % cs;
-            c = ((sc + P) / P2) * T - P + (sc + P) % P2;
+            const int k = g.nsc_div.quotient(j), sc = j - k * g.nsc + P;
+            a0 = g.core.quotient(k);
+            pr = k - a0 * core + P2;
+            b0 = g.P2.quotient(sc);
+            pc = sc - b0 * P2;
             seam_r = false;
         }
         const bool live = idx < n_all;
-        out[i] = live ? r * w + c : -1;
-        const bool seam_c = (c + P) % T < P2;
-        const int a0 = (r + P) / T, b0 = (c + P) / T;
+        out[i] = live ? (a0 * T - P + pr) * w + b0 * T - P + pc : -1;
+        const bool seam_c = pc < P2;
 #pragma unroll
         for (int da = 1; da >= 0; --da) {
             const int a = a0 - da;
-            int p = r - a * T - P;
+            int p = pr - P2 + da * T;
             if (p < 0) p += L;
             const bool ok_a = live && (!da || seam_r) && a >= 0 && a < th;
 #pragma unroll
             for (int db = 1; db >= 0; --db) {
                 const int b = b0 - db;
-                int qq = c - b * T - P;
+                int qq = pc - P2 + db * T;
                 if (qq < 0) qq += L;
                 const bool ok = ok_a && (!db || seam_c) && b >= 0 && b < tw;
                 const unsigned off =
@@ -994,9 +1013,11 @@ hipError_t launch_seam(const fftsplit_plan_s& p, const float* aux, const float* 
     const long long bpp = count > 0 ? (count + per_block - 1) / per_block : 1;
     const long long blocks = bpp * p.prob.n * p.prob.cout;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    // (a divisor of 0 belongs to an enumeration without pixels)
+    const SeamGeometry g{nsr, nsc, int(bpp), fast_div(p.prob.w), fast_div(nsc), fast_div(T), fast_div(P2),
+                         fast_div(T - P2)};
     return launch_kernel(seam_kernel, dim3(unsigned(blocks)), dim3(256), 0, s, nullptr, stop, aux, bias, y,
-                         p.prob.cout, p.prob.h, p.prob.w, p.T, p.P, p.L, p.th, p.tw, p.ntp, int(p.relu), nsr, nsc,
-                         int(bpp));
+                         p.prob.cout, p.prob.h, p.prob.w, p.T, p.P, p.L, p.th, p.tw, p.ntp, int(p.relu), g);
 }
 
 template <int L, int TG>

@@ -4,6 +4,8 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
+
 namespace fftsplit {
 
 // MI355X dispatches consecutive workgroup ids round-robin over its 8
@@ -19,6 +21,26 @@ __device__ __forceinline__ int xcd_logical_block(int hw_block, int nb) {
     const int x = hw_block % kNumXcd;
     const int i = hw_block / kNumXcd;
     return x * q + (x < r ? x : r) + i;
+}
+
+// Quotient of 0 <= n < 2^31 by a divisor d known on the host, as a high
+// product (the division by multiplication of Granlund and Montgomery, 1994):
+// with 2^(l-1) < d <= 2^l and m = floor(2^(31+l) / d) + 1 (below 2^32),
+// m d - 2^(31+l) <= d <= 2^l, so floor(n m / 2^(31+l)) is exact.  d < 2
+// leaves n as it is.
+struct FastDiv {
+    unsigned m, shift;
+    __host__ __device__ __forceinline__ int quotient(int n) const {
+        const unsigned q = unsigned((uint64_t(unsigned(n)) * m) >> 32) >> shift;
+        return m ? int(q) : n;
+    }
+};
+
+inline FastDiv fast_div(int d) {
+    if (d < 2) return FastDiv{0, 0};
+    unsigned l = 1;
+    while ((1LL << l) < d) ++l;
+    return FastDiv{unsigned((1ULL << (31 + l)) / unsigned(d) + 1), l - 1};
 }
 
 // Allows a kernel to use more than the default dynamic LDS once per process.
