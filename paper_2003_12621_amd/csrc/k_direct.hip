@@ -353,7 +353,9 @@ template <int NW>
 static hipError_t launch_direct_split(const fftsplit_plan_s& p, const float* x, const float* wd, const float* bias,
                                       float* y, hipStream_t s, const LaunchEvents& ev, int ltw, int lds) {
     auto kern = direct_split_kernel<NW>;
-    const hipError_t attr = allow_dynamic_lds(kern, lds);
+    // the most that the plan's rule takes, not this filter's: plans of other
+    // filters may launch at the same time
+    const hipError_t attr = allow_dynamic_lds(kern, lds > 64 * 1024 ? 80 * 1024 : lds);
     if (attr != hipSuccess) return attr;
     const int tw = 1 << ltw, th = 64 >> ltw;
     const int tiles_h = (p.prob.h + th - 1) / th, tiles_w = (p.prob.w + tw - 1) / tw;

@@ -26,7 +26,8 @@ CASES = [
     (2, 47, 76, 128, 250, 3),      # 4x16 blocks, four waves, a last group of 16 channels
     (8, 20, 17, 124, 250, 3),      # 1x64 blocks, four waves
     (6, 70, 63, 95, 190, 3),       # a partial last group
-    (11, 96, 40, 40, 256, 9),      # the largest filter
+    (11, 96, 40, 40, 256, 9),      # a large filter
+    (4, 32, 64, 64, 256, 13),      # the largest one: more than 64 KB of LDS
     (40, 30, 14, 60, 120, 3),      # 2x32 blocks, two waves
 ]
 
