@@ -378,9 +378,18 @@ static hipError_t launch_split_v(const fftsplit_plan_s& p, const float2* xs, con
     static_assert(lds <= 160 * 1024 && (KG - 1) * 2 * TM * TN * S::NT * 16 <= lds, "fits the LDS");
     if (p.coutp % BM != 0 || p.ntp % BN != 0) return hipErrorInvalidValue;
     const int nbco = p.coutp / BM, nbt = p.ntp / BN;
-    // Spectra that at most two workgroups (filter) or one (patches) read are
-    // streamed past the caches, as in contract_kernel.
-    auto kern = nbt <= 2 ? (nbco == 1 ? contract_split_kernel<BM, BN, TM, TN, PF, KG, true, true>
+    // Patch spectra that one workgroup reads are streamed past the caches, and
+    // filter spectra that at most two read, or one on tiles of up to 64 x 64:
+    // streamed, the second of those two workgroups often fetches the block
+    // from memory again, which costs more than keeping it where such tiles
+    // leave the compute units waiting for loads.  Whole layers in us, streamed
+    // and kept at two readers: 4x512x28^2 T = 6 69.7, 67.3; 2x300x40^2 T = 6
+    // 46.8, 44.9; 1x300x40^2 K=5 T = 4 45.9, 44.1; 7x30x50^2 -> 512 54.4,
+    // 53.7; on larger tiles 16x256x56^2 T = 14 136.4, 137.7; 64x512x28^2 410,
+    // 416; 2x256x112^2 77.7, 78.7.  (blocks of padding patches read nothing)
+    const int readers = (p.nt + BN - 1) / BN;
+    const bool w_stream = readers <= (BM * BN <= 64 * 64 ? 1 : 2);
+    auto kern = w_stream ? (nbco == 1 ? contract_split_kernel<BM, BN, TM, TN, PF, KG, true, true>
                                       : contract_split_kernel<BM, BN, TM, TN, PF, KG, true, false>)
                          : (nbco == 1 ? contract_split_kernel<BM, BN, TM, TN, PF, KG, false, true>
                                       : contract_split_kernel<BM, BN, TM, TN, PF, KG, false, false>);
