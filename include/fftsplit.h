@@ -144,8 +144,10 @@ typedef struct {
      * plan time, and on the shapes where it is the faster one (patches
      * padded to 32 only, three or four whole channel blocks in a small grid);
      * otherwise the same product runs on the bf16 matrix instruction with
-     * every fp32 operand split exactly into three bf16 parts, and is no less
-     * precise. */
+     * every fp32 operand, subnormal ones too, split exactly into three bf16
+     * parts, and is no less precise.  Where operands or sums are not finite, or
+     * operands reach 2^104 or sums 2^80, the affected part of the product is
+     * computed on the fp32 instruction. */
     int contract_tile_m, contract_tile_n, contract_stage_k, contract_real_products;
     int spec_group;      /* G of the output-spectra layout */
     /* 1 if fftsplit_conv2d sums the input channels inside the inverse stage

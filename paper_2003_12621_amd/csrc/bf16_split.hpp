@@ -7,9 +7,12 @@
 
 #include <hip/hip_runtime.h>
 
+#include "launch_util.hpp"
+
 namespace fftsplit {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -34,6 +37,27 @@ __device__ __forceinline__ void split3(float a, float b, unsigned (&p)[3]) {
 
 __device__ __forceinline__ floatx4 mfma_bf16(u32x4 a, u32x4 b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Operands are split times kSplitScale: bf16 has fp32's exponent range but
+// multiples of 2^-133 only, so of an operand below 2^-110 parts would be lost.
+// Scaled, every fp32 number, subnormal ones too, is the exact sum of its parts,
+// and a sum comes out times kSplitScale^2, which the epilogue takes off again.
+// Operands from 2^104 and sums from 2^80 overflow, and infinities have the
+// parts (inf, NaN, NaN): a wave whose sums are not all finite computes its
+// tile again on the fp32 instruction.
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
+
+// Whether all N values of the wave are finite, the same in every lane.
+template <int N>
+__device__ __forceinline__ bool all_finite(const floatx4* a) {
+    float top = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        top = vmax3(top, __builtin_fabsf(a[i][0]), __builtin_fabsf(a[i][1]));
+        top = vmax3(top, __builtin_fabsf(a[i][2]), __builtin_fabsf(a[i][3]));
+    }
+    return __ballot(!(top < __builtin_inff())) == 0;
 }
 
 }  // namespace fftsplit

@@ -12,9 +12,10 @@
 // the channels, where the sum is large, a block is therefore summed from zero
 // and then added in fp32.  Error over the layers of a VGG-16 stack at batch 4
 // and 32, against the fp32 kernel's: 0.67-0.96 of it; with every block from
-// zero 0.36-0.70, but 4-8 % slower.  bf16 has fp32's exponent range, so
-// no operand needs scaling (operands below 2^-110 lose their smallest parts
-// to underflow).
+// zero 0.36-0.70, but 4-8 % slower.  Operands are scaled by a power of two, so
+// that no part underflows, and a wave whose sums are not all finite computes its
+// tile again on the fp32 instruction, with contract_kernel's products and order
+// (bf16_split.hpp): infinities and NaN come out as there.
 //
 // A complex value (re, im) is one dword of two bf16, and the two sit side by
 // side along the matrix instruction's reduction (k = 2 ci, 2 ci + 1), so
@@ -32,8 +33,8 @@
 //
 // A workgroup tile is BM channels x BN patches of one bin, wave tiles of
 // 16 TM x 16 TN; channel blocks are loaded PF ahead straight into LDS as
-// fp32 and split after the LDS read.  At 64 x 64 a wave issues 400 vector
-// instructions of splits (and 128 additions where a block is summed from zero)
+// fp32 and split after the LDS read.  At 64 x 64 a wave issues 464 vector
+// instructions of splits, 64 of them for the scale (and 128 additions where a block is summed from zero)
 // beside 384 matrix instructions of 16 cycles per channel block, which two
 // waves per SIMD overlap.  With KG > 1, KG wave groups take the channel blocks
 // in turn and add their sums through LDS: more waves on a compute unit that
@@ -98,6 +99,14 @@ __device__ __forceinline__ void split_dma16(uint64_t base, unsigned voff, const 
     else
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(m0)
                      : "memory", "m0");
+}
+
+// The lane's number, computed anew: what only the rare paths and the epilogue
+// need of it is not held in registers through the loop.
+__device__ __forceinline__ int fresh_lane() {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
 }
 
 // A 64-bit address that is the same in every lane, in scalar registers.
@@ -192,6 +201,7 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
 #pragma unroll
             for (int i = 0; i < S::XL; ++i) split_dma16<XS>(xb + uint64_t(i * S::XROWS) * xrow, xvoff, sx + i * NT);
         } else {
+            const int tid = 64 * wave + fresh_lane();
 #pragma unroll
             for (int i = 0; i < S::WL; ++i) {
                 const int c = i * S::WROWS + tid / (BM / 2);
@@ -220,8 +230,8 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
             for (int c = 0; c < 4; ++c) {
                 const float4 v = *reinterpret_cast<const float4*>(sw + c * BM + 32 * p);
                 unsigned q0[3], q1[3];
-                split3(v.x, v.y, q0);
-                split3(v.z, v.w, q1);
+                split3(v.x * kSplitScale, v.y * kSplitScale, q0);
+                split3(v.z * kSplitScale, v.w * kSplitScale, q1);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
                     a[q][2 * p][c] = q0[q];
@@ -240,7 +250,8 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     unsigned qr[3], qi[3];
-                    split_patch<decltype(packed)::value>(e ? v[c].z : v[c].x, e ? v[c].w : v[c].y, qr, qi);
+                    split_patch<decltype(packed)::value>((e ? v[c].z : v[c].x) * kSplitScale,
+                                                         (e ? v[c].w : v[c].y) * kSplitScale, qr, qi);
 #pragma unroll
                     for (int q = 0; q < 3; ++q) {
                         br[q][c] = qr[q];
@@ -277,6 +288,7 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
         const int s = it * KG + group;
         if (s < nstage) dma_stage(s, buffer(it));
     };
+    // Whether the wave's sums are finite (bf16_split.hpp), and stored.
     auto run = [&](auto packed) __attribute__((always_inline)) {
         floatx4 accR[TM][TN], accI[TM][TN];
 #pragma unroll
@@ -302,7 +314,7 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
                 if (it == nit - 1 && cin % KC != 0) {
                     // the partial block's missing filter rows (only its own
                     // group's; the barrier is everyone's)
-                    const int last = cin - 1 - s * KC;
+                    const int last = cin - 1 - s * KC, tid = 64 * wave + fresh_lane();
 #pragma unroll
                     for (int i = 0; i < S::WL; ++i)
                         if (i * S::WROWS + tid / (BM / 2) > last)
@@ -322,6 +334,7 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
         if constexpr (KG > 1) {
             // the groups' partial sums, through LDS to the first group
             constexpr int NA = 2 * TM * TN;
+            const int tid = 64 * wave + fresh_lane();
             floatx4* part = reinterpret_cast<floatx4*>(lds_raw) + tid;
             __syncthreads();
             if (group > 0) {
@@ -334,7 +347,7 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
                     }
             }
             __syncthreads();
-            if (group > 0) return;
+            if (group > 0) return true;
 #pragma unroll
             for (int g = 0; g < KG - 1; ++g)
 #pragma unroll
@@ -345,6 +358,9 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
                         accI[i][j] += part[(g * NA + 2 * (i * TN + j) + 1) * NT];
                     }
         }
+
+        const int lane = fresh_lane(), quad = lane >> 4, col = lane & 15;
+        if (!all_finite<TM * TN>(&accR[0][0]) || !all_finite<TM * TN>(&accI[0][0])) return false;
 
         // Output spectra (patch-group-major): D register r of lane (quad,
         // col) is row 4 quad + r, column col of its 16 x 16 block, so a lane
@@ -360,14 +376,42 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    buf_store_f32x4(make_float4(accR[i][j][r], accI[i][j][r], accR[i][j + 1][r], accI[i][j + 1][r]), ry,
+                    buf_store_f32x4(make_float4(accR[i][j][r] * kSplitUnscale, accI[i][j][r] * kSplitUnscale,
+                                                accR[i][j + 1][r] * kSplitUnscale, accI[i][j + 1][r] * kSplitUnscale), ry,
                                     voff, unsigned(32 * (i / 2) + 2 * r + i % 2) * cs8);
         }
+        return true;
     };
     // one loop for each kind of bin (a branch inside the loop would merge the
     // accumulators of its two sides by copies)
-    if (f >= nbins - npacked) run(std::true_type{});
-    else run(std::false_type{});
+    const bool two_real = f >= nbins - npacked;
+    if (two_real ? run(std::true_type{}) : run(std::false_type{})) return;
+
+    // The wave's tile on the fp32 instruction, operands from memory: the
+    // products and the order of contract_kernel with three real products.
+    const int krow = fresh_lane() >> 5, l32 = fresh_lane() & 31;
+    for (int blk = 0; blk < (TM / 2) * (TN / 2); ++blk) {
+        const int co = co0 + wm * (16 * TM) + blk / (TN / 2) * 32, t = t0 + wn * (16 * TN) + blk % (TN / 2) * 32;
+        floatx16 p1, p2, p3;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) p1[r] = p2[r] = p3[r] = 0.f;
+        for (int c0 = 0; c0 < cin; c0 += 2) {
+            const int c = c0 + krow;
+            float2 a = make_float2(0.f, 0.f), b = a;
+            if (c < cin) {
+                a = ws[(size_t(f) * cin + c) * coutp + co + l32];
+                b = xs[spec_offset(c, f, t + l32, nbins, ntp)];
+            }
+            p1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, p1, 0, 0, 0);
+            p2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, p2, 0, 0, 0);
+            p3 = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x + a.y, b.x + b.y, p3, 0, 0, 0);
+        }
+        float2* dst = ys + yspec_offset(co + 4 * krow, f, t + l32, nbins, ygroup, ntp / ygroup);
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            dst[size_t(8 * (r >> 2) + (r & 3)) * nbins * ntp] =
+                two_real ? make_float2(p1[r], p2[r]) : make_float2(p1[r] - p2[r], p3[r] - p1[r] - p2[r]);
+    }
 }
 
 template <int BM, int BN, int TM, int TN, int PF, int KG = 1>
