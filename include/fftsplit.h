@@ -279,9 +279,10 @@ fftsplit_status_t fftsplit_inverse(fftsplit_plan_t plan, const float* bias, floa
 /* The spatial convolution the paper compares the split method against
  * (Section 2, eq. 1 computed directly; Section 4): the same layer as the
  * plan's, as an implicit matrix product in fp32 (on the fp32 matrix
- * instruction, or on the bf16 one with every operand split exactly into three
- * parts where that is faster: no less precise), with the plan's bias and ReLU flags.  The filters are first rearranged once per
- * layer:
+ * instruction, or where that is faster on the bf16 one with every operand,
+ * subnormal ones too, split exactly into three parts: no less precise, and
+ * back on the fp32 one where a sum is not finite), with the plan's bias and
+ * ReLU flags.  The filters are first rearranged once per layer:
  *   fftsplit_direct_transform_weights: w (device) [cout][cin][k][k] ->
  *     wd (device, info.direct_wspec_bytes) = [k*k][cin16][cout_padded],
  *     zero for padded channels;

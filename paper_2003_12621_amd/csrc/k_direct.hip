@@ -145,7 +145,7 @@ __global__ __launch_bounds__(256) void direct_kernel(const float* __restrict__ x
 }
 
 // The same convolution on the bf16 matrix instruction (bf16_split.hpp), for
-// filters up to 9 x 9: an fp32 result from six part products per product.
+// filters up to 13 x 13: an fp32 result from six part products per product.
 // A workgroup owns NW * 64 output channels x 64 pixels (a th x tw block of
 // one image), a wave 64 x 64.  Per group of 32 input channels the block's
 // pixels and their halo are split once into LDS, part by part and octet of
@@ -154,11 +154,11 @@ __global__ __launch_bounds__(256) void direct_kernel(const float* __restrict__ x
 // neighbouring 16 bytes), and all K * K taps read them there at shifted
 // addresses.  The filter operand (channels 8 quad + 0..7 of rows 4 col + 0..3:
 // eight 16-byte loads of the re-laid filters, one tap ahead) is split in
-// registers: 176 vector instructions against 96 matrix instructions of 16
-// cycles, which two waves per SIMD overlap.
-// The parts of an infinity are (inf, NaN, NaN) and an infinite part times a
-// zero part is NaN, so a wave whose sums are not all finite computes its
-// block again on the fp32 instruction, in direct_kernel's order.
+// registers: 208 vector instructions against 96 matrix instructions of 16
+// cycles, which two waves per SIMD overlap.  Pixels and filters are scaled
+// before they are split (bf16_split.hpp), and a wave whose sums are not all
+// finite computes its block again on the fp32 instruction, in direct_kernel's
+// order.
 // Bound: the matrix cores (clock 2.0 GHz under them) and the vector work
 // beside them.  16x256x56^2 -> 256, K = 5: 1754 us on the fp32 instruction,
 // 945 us here (174 TFLOP/s of the convolution's operations); 8x128x112^2
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(64 * NW, 2) void direct_split_kernel(
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 unsigned p[3];
-                split3(v[2 * d], v[2 * d + 1], p);
+                split3(v[2 * d] * kSplitScale, v[2 * d + 1] * kSplitScale, p);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) s[q][d] = p[q];
             }
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(64 * NW, 2) void direct_split_kernel(
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     unsigned p[3];
-                    split3(e0[i], e1[i], p);
+                    split3(e0[i] * kSplitScale, e1[i] * kSplitScale, p);
 #pragma unroll
                     for (int q = 0; q < 3; ++q) a[q][i][d] = p[q];
                 }
@@ -296,21 +296,14 @@ __global__ __launch_bounds__(64 * NW, 2) void direct_split_kernel(
         if (relu) v = vmax(v, 0.f);
         buf_store_f32(v, ry, co < cout && px != kOutOfRange ? px + unsigned(co * hw) * 4u : kOutOfRange, 0);
     };
-    bool finite = true;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int n = 0; n < 4; ++n)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) finite &= __builtin_fabsf(acc[i][n][r]) < __builtin_inff();
-    if (__ballot(!finite) == 0) {
+    if (all_finite<16>(&acc[0][0])) {
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
             const unsigned px = pixel(16 * n + col);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) store(acc[i][n][r], co0 + 4 * (4 * quad + r) + i, px);
+                for (int i = 0; i < 4; ++i) store(acc[i][n][r] * kSplitUnscale, co0 + 4 * (4 * quad + r) + i, px);
         }
         return;
     }
