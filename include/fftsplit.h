@@ -140,14 +140,15 @@ typedef struct {
      * stages of contract_stage_k, and 3 (Gauss) or 4 real matrix products
      * per complex multiply-add.  It runs where the environment variable
      * FFTSPLIT_CONTRACT_TILE=[g3:|g4:]MxNxK (which overrides the choice),
-     * FFTSPLIT_CONTRACT_PREFETCH or FFTSPLIT_CONTRACT_SPLIT=0 asks for it at
-     * plan time, and on the shapes where it is the faster one (patches
-     * padded to 32 only, three or four whole channel blocks in a small grid);
-     * otherwise the same product runs on the bf16 matrix instruction with
-     * every fp32 operand, subnormal ones too, split exactly into three bf16
-     * parts, and is no less precise.  Where operands or sums are not finite, or
-     * operands reach 2^104 or sums 2^80, the affected part of the product is
-     * computed on the fp32 instruction. */
+     * FFTSPLIT_CONTRACT_PREFETCH=1..3 or FFTSPLIT_CONTRACT_SPLIT=0 asks for it
+     * at plan time, where the patches are padded to an odd multiple of 32, and
+     * for three or four whole channel blocks in a small grid; otherwise the
+     * same product runs on the bf16 matrix instruction with every fp32
+     * operand, subnormal ones too, split exactly into three bf16 parts, and is
+     * no less precise.  Where operands or sums are not finite, or operands
+     * reach 2^104 or sums 2^80, the affected part of the product is computed
+     * on the fp32 instruction.  fftsplit_plan_kernels tells which one a plan
+     * runs. */
     int contract_tile_m, contract_tile_n, contract_stage_k, contract_real_products;
     int spec_group;      /* G of the output-spectra layout */
     /* 1 if fftsplit_conv2d sums the input channels inside the inverse stage
@@ -159,7 +160,7 @@ typedef struct {
     /* Bytes of the filter layout of the direct (spatial) convolution,
      * fftsplit_direct_transform_weights. */
     size_t direct_wspec_bytes;
-    /* Input-channel stages the contraction loads ahead of the one it
+    /* Input-channel stages the fp32 contraction loads ahead of the one it
      * multiplies: 1 (through registers), or 2 or 3 straight into LDS (2 the
      * default where the tile has that variant, 3 with the 8-channel stages
      * the plan picks for layers of at most 128 input channels and at least
@@ -223,6 +224,30 @@ fftsplit_status_t fftsplit_plan_for_arch(const fftsplit_problem_t* prob, const c
  * and layouts the caller must provide, and the kernel variants.  Fails with
  * FFTSPLIT_ERROR_INVALID_VALUE on a NULL argument. */
 fftsplit_status_t fftsplit_plan_info(fftsplit_plan_t plan, fftsplit_plan_info_t* out /* host */);
+
+/* The matrix kernels that a plan's entry points launch (fftsplit_plan_info_t
+ * describes the fp32 contraction kernel, also for a plan that does not run
+ * it). */
+typedef struct {
+    /* fftsplit_contract (and fftsplit_conv2d, unless fused_channel_sum): 1 if
+     * on the bf16 matrix instruction with fp32 operands split into three parts,
+     * 0 if on the fp32 one.  A workgroup's output tile is contract_tile_m
+     * channels x contract_tile_n patches; the input channels are taken in
+     * stages of contract_stage_k, contract_prefetch of them loaded ahead, by
+     * contract_wave_groups groups of waves in turn.  A complex multiply-add
+     * takes contract_real_products real matrix products of
+     * contract_part_products instructions' work each. */
+    int contract_split;
+    int contract_tile_m, contract_tile_n, contract_stage_k, contract_prefetch, contract_wave_groups;
+    int contract_real_products, contract_part_products;
+    /* fftsplit_direct_conv2d: 1 if on the bf16 matrix instruction, in blocks
+     * of 64 pixels that are direct_block_w wide; 0 (and 0) if on the fp32 one,
+     * in runs of pixels. */
+    int direct_split, direct_block_w;
+} fftsplit_plan_kernels_t;
+
+/* Fails with FFTSPLIT_ERROR_INVALID_VALUE on a NULL argument. */
+fftsplit_status_t fftsplit_plan_kernels(fftsplit_plan_t plan, fftsplit_plan_kernels_t* out /* host */);
 
 /* Frees a plan's host memory.  NULL is ignored. */
 void fftsplit_plan_destroy(fftsplit_plan_t plan);
@@ -318,13 +343,15 @@ fftsplit_status_t fftsplit_set_timing_events(hipEvent_t start, hipEvent_t stop);
  * of the method.
  *
  * fftsplit_probe_matrix: enqueues on `stream` (on the plan's device) one
- * kernel with the plan's contraction launch -- the same grid of 256-thread
- * workgroups and the same dynamic LDS, hence the same workgroups per
- * compute unit -- in which every wave issues as many fp32 matrix
- * operations (v_mfma_f32_32x32x2f32) as a wave of fftsplit_contract does,
- * with operands in registers and no other memory traffic.  Its duration is
- * the time the matrix cores need for the contraction's executed
- * operations at this launch shape.  `sink` (device, one float) is written
+ * kernel with the launch of the plan's fp32 contraction kernel (the
+ * contract_* fields of fftsplit_plan_info_t, also for a plan whose
+ * fftsplit_contract runs on the bf16 instruction) -- the same grid of
+ * 256-thread workgroups and the same dynamic LDS, hence the same workgroups
+ * per compute unit -- in which every wave issues as many fp32 matrix
+ * operations (v_mfma_f32_32x32x2f32) as a wave of that kernel does, with
+ * operands in registers and no other memory traffic.  Its duration is the
+ * time the fp32 matrix cores need for those operations at this launch
+ * shape.  `sink` (device, one float) is written
  * only if the sum of a wave's accumulators is exactly -1, which it never
  * is.  INVALID_VALUE for a NULL plan or sink or an architecture-only plan;
  * NOT_SUPPORTED for a plan whose channel sum runs inside the inverse (it

@@ -65,6 +65,13 @@ class PlanInfo(ctypes.Structure):
                 ("forward_stream", ctypes.c_int)]
 
 
+class PlanKernels(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_int) for f in
+                ("contract_split", "contract_tile_m", "contract_tile_n", "contract_stage_k", "contract_prefetch",
+                 "contract_wave_groups", "contract_real_products", "contract_part_products", "direct_split",
+                 "direct_block_w")]
+
+
 class FftsplitError(RuntimeError):
     def __init__(self, status: int, where: str, detail: str):
         self.status = status
@@ -79,6 +86,7 @@ _SIGNATURES = {
     "fftsplit_plan_for_arch": (ctypes.c_int, [ctypes.POINTER(Problem), ctypes.c_char_p,
                                               ctypes.POINTER(ctypes.c_void_p)]),
     "fftsplit_plan_info": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(PlanInfo)]),
+    "fftsplit_plan_kernels": (ctypes.c_int, [ctypes.c_void_p, ctypes.POINTER(PlanKernels)]),
     "fftsplit_plan_destroy": (None, [ctypes.c_void_p]),
     "fftsplit_transform_weights": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
                                                   ctypes.c_void_p]),
@@ -214,6 +222,13 @@ class Plan:
     def nfft(self) -> int:
         return self.info.nfft
 
+    @property
+    def kernels(self) -> PlanKernels:
+        """The matrix kernels this plan's entry points launch."""
+        out = PlanKernels()
+        _check(lib().fftsplit_plan_kernels(self._h, ctypes.byref(out)), "fftsplit_plan_kernels")
+        return out
+
     def new_workspace(self):
         torch = _torch()
         return torch.empty(self.info.workspace_bytes, dtype=torch.uint8, device=self.device)
@@ -327,8 +342,8 @@ class Plan:
 
     # -- measurement hook ---------------------------------------------------
     def probe_matrix(self, sink=None):
-        """Enqueue the matrix-core probe of this plan's contraction launch
-        (fftsplit_probe_matrix): same grid and occupancy, the same fp32
+        """Enqueue the matrix-core probe of this plan's fp32 contraction
+        kernel (fftsplit_probe_matrix): same grid and occupancy, the same fp32
         matrix operations per wave, no memory traffic.  `sink`: a CUDA
         float32 tensor of at least one element (allocated if None)."""
         torch = _torch()

@@ -414,9 +414,11 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
     }
 }
 
-template <int BM, int BN, int TM, int TN, int PF, int KG = 1>
+template <SplitTile TILE, int TM, int TN>
 static hipError_t launch_split_v(const fftsplit_plan_s& p, const float2* xs, const float2* ws, float2* ys,
                                  hipStream_t s, const LaunchEvents& ev) {
+    constexpr SplitTileShape V = kSplitTileShapes[TILE];
+    constexpr int BM = V.bm, BN = V.bn, PF = V.ahead, KG = V.groups;
     using S = SplitShape<BM, BN, TM, TN>;
     constexpr int lds = KG * (PF + 1) * S::STAGE * 8;
     static_assert(lds <= 160 * 1024 && (KG - 1) * 2 * TM * TN * S::NT * 16 <= lds, "fits the LDS");
@@ -447,22 +449,15 @@ static hipError_t launch_split_v(const fftsplit_plan_s& p, const float2* xs, con
 hipError_t launch_contract_split(const fftsplit_plan_s& p, const float2* xs, const float2* ws, float2* ys,
                                  hipStream_t s, const LaunchEvents& ev) {
     switch (p.con_split) {
-        case kSplit128x128: return launch_split_v<128, 128, 4, 4, 1, 1>(p, xs, ws, ys, s, ev);
-        case kSplit256x64: return launch_split_v<256, 64, 4, 4, 1, 1>(p, xs, ws, ys, s, ev);
-        case kSplit64x256: return launch_split_v<64, 256, 4, 4, 1, 1>(p, xs, ws, ys, s, ev);
-        case kSplit128x64: return launch_split_v<128, 64, 4, 2, 1, 1>(p, xs, ws, ys, s, ev);
-        case kSplit64x64:
-            // two stages ahead (three workgroups on a compute unit) where
-            // there are more than four to load or the grid is no larger than
-            // that (the whole 1x64x224^2 layer: 28.4 us, one stage ahead
-            // 29.4); one ahead and four workgroups otherwise (the whole
-            // 11x119x182x55 -> 24 layer: 69.8, two ahead 71.8)
-            if (p.prob.cin > 4 * kChanBlock || size_t(p.coutp / 64) * (p.ntp / 64) * p.bins <= size_t(3) * p.cus)
-                return launch_split_v<64, 64, 2, 2, 2, 1>(p, xs, ws, ys, s, ev);
-            return launch_split_v<64, 64, 2, 2, 1, 1>(p, xs, ws, ys, s, ev);
-        case kSplit64x64g2: return launch_split_v<64, 64, 2, 2, 1, 2>(p, xs, ws, ys, s, ev);
-        case kSplit64x32g2: return launch_split_v<64, 32, 2, 2, 1, 2>(p, xs, ws, ys, s, ev);
-        case kSplit64x32g4: return launch_split_v<64, 32, 2, 2, 1, 4>(p, xs, ws, ys, s, ev);
+        case kSplit128x128: return launch_split_v<kSplit128x128, 4, 4>(p, xs, ws, ys, s, ev);
+        case kSplit256x64: return launch_split_v<kSplit256x64, 4, 4>(p, xs, ws, ys, s, ev);
+        case kSplit64x256: return launch_split_v<kSplit64x256, 4, 4>(p, xs, ws, ys, s, ev);
+        case kSplit128x64: return launch_split_v<kSplit128x64, 4, 2>(p, xs, ws, ys, s, ev);
+        case kSplit64x64: return launch_split_v<kSplit64x64, 2, 2>(p, xs, ws, ys, s, ev);
+        case kSplit64x64a2: return launch_split_v<kSplit64x64a2, 2, 2>(p, xs, ws, ys, s, ev);
+        case kSplit64x64g2: return launch_split_v<kSplit64x64g2, 2, 2>(p, xs, ws, ys, s, ev);
+        case kSplit64x32g2: return launch_split_v<kSplit64x32g2, 2, 2>(p, xs, ws, ys, s, ev);
+        case kSplit64x32g4: return launch_split_v<kSplit64x32g4, 2, 2>(p, xs, ws, ys, s, ev);
         case kSplitNone: break;
     }
     return hipErrorInvalidValue;

@@ -1,10 +1,10 @@
 // Measurement hooks: the practical ceilings the path's kernels are measured
 // against, on the chip they run on.  Neither is part of the method.
 //
-// matrix_probe_kernel: the contraction's launch (same grid, 256 threads,
+// matrix_probe_kernel: the fp32 contraction kernel's launch (same grid, 256 threads,
 // same dynamic LDS, hence the same workgroups per compute unit) with each
 // wave issuing the same number of v_mfma_f32_32x32x2f32 operations as a
-// contraction wave, from registers, with no memory traffic: the rate the
+// wave of that kernel, from registers, with no memory traffic: the rate the
 // fp32 matrix cores sustain for this launch shape, fill and drain included.
 //
 // stream_probe_kernel: a plain streaming kernel that reads R and writes W

@@ -172,18 +172,13 @@ static void choose_forward_band(fftsplit_plan_s& p) {
     p.fwd_lds = int(lds);
 }
 
-static const char* split_tile_name(int tile) {
-    switch (tile) {
-        case kSplit128x128: return "split 128x128";
-        case kSplit256x64: return "split 256x64";
-        case kSplit64x256: return "split 64x256";
-        case kSplit128x64: return "split 128x64";
-        case kSplit64x64: return "split 64x64";
-        case kSplit64x64g2: return "split 64x64/2";
-        case kSplit64x32g2: return "split 64x32/2";
-        case kSplit64x32g4: return "split 64x32/4";
-    }
-    return "fp32";
+static std::string contract_name(const fftsplit_plan_s& p) {
+    if (!p.con_split) return "fp32";
+    const SplitTileShape& v = kSplitTileShapes[p.con_split];
+    std::string name = "split " + std::to_string(v.bm) + "x" + std::to_string(v.bn);
+    if (v.ahead > 1) name += " +" + std::to_string(v.ahead);
+    if (v.groups > 1) name += "/" + std::to_string(v.groups);
+    return name;
 }
 
 // The tile of the bf16-split contraction, by the number of workgroups it
@@ -210,6 +205,10 @@ static const char* split_tile_name(int tile) {
 // compute unit stay on the fp32 kernel, whose whole sum is loaded at once and
 // whose waves have the shorter chain (the whole 1x64x224^2 layer: 28.8 us,
 // 64x64 split 29.3).
+// The single-group 64x64 tile loads two stages ahead (three workgroups on a
+// compute unit) where there are more than four to load or the grid is no larger
+// than that, one ahead (four workgroups) otherwise: the whole 11x119x182x55 ->
+// 24 layer 69.8 us, two ahead 71.8.
 // An explicit FFTSPLIT_CONTRACT_TILE or _PREFETCH, or
 // FFTSPLIT_CONTRACT_SPLIT=0, selects the fp32 kernel instead.
 static void choose_contract_split(fftsplit_plan_s& p) {
@@ -232,6 +231,8 @@ static void choose_contract_split(fftsplit_plan_s& p) {
     else if (p.prob.cin <= 4 * kChanBlock && p.prob.cin % kChanBlock == 0 && blocks(64, 64) <= size_t(3) * p.cus) return;
     else if (p.prob.cin <= 4 * kChanBlock || blocks(64, 64) > kFull) p.con_split = kSplit64x64;
     else p.con_split = kSplit64x64g2;
+    if (p.con_split == kSplit64x64 && (p.prob.cin > 4 * kChanBlock || blocks(64, 64) <= size_t(3) * p.cus))
+        p.con_split = kSplit64x64a2;
 }
 
 // The direct convolution's kernel.  The bf16 one takes 32 input channels a
@@ -503,7 +504,7 @@ static fftsplit_status_t build_plan(const fftsplit_problem_t* prob, int device, 
                      "[fftsplit] plan n=%d cin=%d %dx%d cout=%d k=%d -> T=%d L=%d tiles=%d(%d) bins=%d %s "
                      "model=%.1f us wspec=%zu ws=%zu contract=%s\n",
                      p.n, p.cin, p.h, p.w, p.cout, p.k, g.T, g.L, g.nt, g.ntp, g.bins, oaa ? "oaa" : "os",
-                     g.model_seconds * 1e6, wsb, plan->ws_bytes, split_tile_name(plan->con_split));
+                     g.model_seconds * 1e6, wsb, plan->ws_bytes, contract_name(*plan).c_str());
     }
     *out = plan;
     return FFTSPLIT_SUCCESS;
@@ -563,6 +564,37 @@ FFTSPLIT_EXPORT fftsplit_status_t fftsplit_plan_info(fftsplit_plan_t plan, fftsp
     i.model_transform_bytes = plan->model_xfer_bytes;
     i.model_seconds = plan->model_seconds;
     *out = i;
+    return FFTSPLIT_SUCCESS;
+}
+
+FFTSPLIT_EXPORT fftsplit_status_t fftsplit_plan_kernels(fftsplit_plan_t plan, fftsplit_plan_kernels_t* out) {
+    set_error("");
+    if (!plan || !out) return fail(FFTSPLIT_ERROR_INVALID_VALUE, "plan and output must be non-NULL");
+    fftsplit_plan_kernels_t k{};
+    if (plan->con_split) {
+        const SplitTileShape& v = kSplitTileShapes[plan->con_split];
+        k.contract_split = 1;
+        k.contract_tile_m = v.bm;
+        k.contract_tile_n = v.bn;
+        k.contract_stage_k = kChanBlock;
+        k.contract_prefetch = v.ahead;
+        k.contract_wave_groups = v.groups;
+        k.contract_real_products = 4;
+        k.contract_part_products = 6;
+    } else {
+        k.contract_tile_m = plan->con_bm;
+        k.contract_tile_n = plan->con_bn;
+        k.contract_stage_k = plan->con_kc;
+        k.contract_prefetch = plan->con_prefetch;
+        k.contract_wave_groups = 1;
+        k.contract_real_products = plan->con_products;
+        k.contract_part_products = 1;
+    }
+    if (plan->dir_ltw) {
+        k.direct_split = 1;
+        k.direct_block_w = 1 << plan->dir_ltw;
+    }
+    *out = k;
     return FFTSPLIT_SUCCESS;
 }
 

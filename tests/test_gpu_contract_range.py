@@ -12,28 +12,21 @@ import pytest
 
 from workloads import small_layer
 
+from test_gpu_contract_split import CASES as SPLIT_CASES
+
 torch = pytest.importorskip("torch")
 fs = pytest.importorskip("paper_2003_12621_amd")
 
 pytestmark = pytest.mark.gpu
 
-CASES = [
-    # (n, cin, h, w, cout, k), tile T
-    ((8, 35, 110, 120, 128, 3), 30),    # 128x128
-    ((4, 47, 100, 100, 256, 3), 30),    # 256x64
-    ((16, 34, 112, 100, 48, 3), 30),    # 64x256
-    ((4, 37, 100, 100, 128, 3), 30),    # 128x64
-    ((20, 50, 56, 56, 40, 3), 14),      # 64x64, one stage ahead
-    ((5, 83, 56, 56, 192, 3), 14),      # 64x64, two ahead
-    ((4, 96, 56, 40, 192, 3), 14),      # 64x64, two groups
-    ((2, 97, 24, 24, 70, 3), 6),        # 64x32, two groups
-    ((1, 270, 24, 24, 70, 3), 6),       # 64x32, four groups
-    ((2, 18, 25, 25, 20, 5), 5),        # no slots of two real bins
-]
+# one shape for each tile, and one whose transforms have no slots of two real bins
+CASES = list({kernel: (shape, tile) for shape, tile, kernel in SPLIT_CASES if shape[1] > 16 and tile != shape[5]}
+             .values()) + [((2, 18, 25, 25, 20, 5), 5)]
 
 
-def _spectra(shape, tile, x, w):
+def _spectra(shape, tile, x, w, split=1):
     plan = fs.Plan(*shape, tile=tile, mode="oaa" if tile == shape[5] else "os")
+    assert plan.kernels.contract_split == split
     ws = plan.new_workspace()
     wspec = plan.transform_weights(torch.from_numpy(w).cuda())
     plan.forward(torch.from_numpy(x).cuda(), ws)
@@ -63,7 +56,7 @@ def test_small_operands(shape, tile, xs, ws, monkeypatch):
     packed = shape[5] != tile
     X, W, Y, _ = _spectra(shape, tile, x, w)
     monkeypatch.setenv("FFTSPLIT_CONTRACT_SPLIT", "0")
-    assert _error(X, W, Y, packed) <= _error(*_spectra(shape, tile, x, w)[:3], packed)
+    assert _error(X, W, Y, packed) <= _error(*_spectra(shape, tile, x, w, 0)[:3], packed)
 
 
 @pytest.mark.parametrize("shape,tile", CASES)
@@ -76,15 +69,15 @@ def test_small_operands_among_ordinary_ones(shape, tile, monkeypatch):
     w[shape[4] // 2] *= np.float32(2.0 ** -112)
     co, packed = shape[4] // 2, shape[5] != tile
 
-    def errors():
-        X, W, Y, plan = _spectra(shape, tile, x, w)
+    def errors(split):
+        X, W, Y, plan = _spectra(shape, tile, x, w, split)
         t = plan.info.tiles - plan.info.tiles_h * plan.info.tiles_w
         return [_error(X[:, :, t:], W[:, :, :co], Y[:, :co, t:], packed),
                 _error(X, W[:, :, co:co + 1], Y[:, co:co + 1], packed) if t == 0 else
                 _error(X[:, :, :t], W[:, :, co:co + 1], Y[:, co:co + 1, :t], packed)]
-    split = errors()
+    split = errors(1)
     monkeypatch.setenv("FFTSPLIT_CONTRACT_SPLIT", "0")
-    for s, f in zip(split, errors()):
+    for s, f in zip(split, errors(0)):
         assert s <= f
 
 
@@ -108,15 +101,15 @@ def test_nonfinite_values_are_the_fp32_kernels(shape, tile, overflow, monkeypatc
         x[::8, :, : tile, : tile] *= np.float32(5)
     b = np.zeros(shape[4], np.float32)
 
-    def run():
-        y = _spectra(shape, tile, x, w)[2]
+    def run(split):
+        y = _spectra(shape, tile, x, w, split)[2]
         plan = fs.Plan(*shape, tile=tile, mode="oaa" if tile == shape[5] else "os", bias=True, relu=True)
         out = plan.conv2d(torch.from_numpy(x).cuda(), plan.transform_weights(torch.from_numpy(w).cuda()),
                           torch.from_numpy(b).cuda())
         return torch.view_as_real(y).contiguous(), out
-    split = run()
+    split = run(1)
     monkeypatch.setenv("FFTSPLIT_CONTRACT_SPLIT", "0")
-    for s, f in zip(split, run()):
+    for s, f in zip(split, run(0)):
         assert not bool(s.isfinite().all())
         same = (s.isnan() == f.isnan()) & (s.isposinf() == f.isposinf()) & (s.isneginf() == f.isneginf())
         assert bool((same | (s.isfinite() & ~f.isfinite()) if overflow else same).all())

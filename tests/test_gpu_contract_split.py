@@ -22,25 +22,34 @@ fs = pytest.importorskip("paper_2003_12621_amd")
 
 pytestmark = pytest.mark.gpu
 
+# (n, cin, h, w, cout, k), tile T, then what the plan's rule gives: channels x
+# patches of the workgroup tile, stages loaded ahead, wave groups
 CASES = [
-    # (n, cin, h, w, cout, k), tile T, the tile the plan's rule gives
-    ((2, 97, 24, 24, 70, 3), 6, "64x32, two groups, a partial block"),
-    ((3, 80, 24, 24, 40, 3), 6, "64x32, two groups, five channel blocks"),
-    ((1, 270, 24, 24, 70, 3), 6, "64x32, four groups, a partial block"),
-    ((3, 256, 24, 24, 40, 3), 6, "64x32, four groups"),
-    ((1, 3, 20, 40, 5, 3), 14, "64x64, one channel block, padding patches"),
-    ((20, 50, 56, 56, 40, 3), 14, "64x64, a partial block"),
-    ((1, 1, 30, 30, 1, 3), 30, "64x64, one channel"),
-    ((5, 83, 56, 56, 192, 3), 14, "64x64, many blocks"),
-    ((3, 83, 56, 56, 64, 3), 14, "64x64, two groups, a partial block"),
-    ((4, 96, 56, 40, 192, 3), 14, "64x64, two groups, even blocks"),
-    ((4, 37, 100, 100, 128, 3), 30, "128x64"),
-    ((4, 47, 100, 100, 256, 3), 30, "256x64"),
-    ((8, 35, 110, 120, 128, 3), 30, "128x128"),
-    ((16, 34, 112, 100, 48, 3), 30, "64x256"),
-    ((2, 18, 25, 25, 20, 5), 5, "64x64, odd transform size: no packed bins"),
-    ((2, 70, 25, 25, 20, 5), 5, "64x32, two groups, odd transform size"),
+    ((2, 97, 24, 24, 70, 3), 6, (64, 32, 1, 2)),      # a partial block
+    ((3, 80, 24, 24, 40, 3), 6, (64, 32, 1, 2)),      # five channel blocks
+    ((1, 270, 24, 24, 70, 3), 6, (64, 32, 1, 4)),     # a partial block
+    ((3, 256, 24, 24, 40, 3), 6, (64, 32, 1, 4)),
+    ((1, 3, 20, 40, 5, 3), 14, (64, 64, 2, 1)),       # one channel block, padding patches
+    ((20, 50, 56, 56, 40, 3), 14, (64, 64, 2, 1)),    # a partial block
+    ((1, 1, 30, 30, 1, 3), 30, (64, 64, 2, 1)),       # one channel
+    ((5, 83, 56, 56, 192, 3), 14, (64, 64, 2, 1)),    # many blocks
+    ((10, 23, 112, 112, 70, 3), 14, (64, 64, 1, 1)),  # two blocks, one of them partial
+    ((30, 50, 56, 56, 40, 3), 14, (64, 64, 1, 1)),    # four blocks
+    ((3, 83, 56, 56, 192, 3), 14, (64, 64, 1, 2)),    # a partial block
+    ((4, 96, 56, 40, 192, 3), 14, (64, 64, 1, 2)),    # even blocks
+    ((4, 37, 100, 100, 128, 3), 30, (128, 64, 1, 1)),
+    ((4, 47, 100, 100, 256, 3), 30, (256, 64, 1, 1)),
+    ((8, 35, 110, 120, 128, 3), 30, (128, 128, 1, 1)),
+    ((16, 34, 112, 100, 48, 3), 30, (64, 256, 1, 1)),
+    ((2, 18, 25, 25, 20, 5), 5, (64, 64, 2, 1)),      # odd transform size: no packed bins
+    ((2, 70, 25, 25, 20, 5), 5, (64, 32, 1, 2)),      # odd transform size
 ]
+
+
+def _tile(plan):
+    k = plan.kernels
+    assert k.contract_split
+    return k.contract_tile_m, k.contract_tile_n, k.contract_prefetch, k.contract_wave_groups
 
 
 def _spectra(shape, tile, scale=1.0, mean=0.0):
@@ -65,10 +74,11 @@ def _channel_sum(X, W, packed):
     return Y, A
 
 
-@pytest.mark.parametrize("shape,tile,what", CASES)
-def test_against_float64(shape, tile, what):
-    print(f"[case] {shape} T={tile} {what}", flush=True)
+@pytest.mark.parametrize("shape,tile,kernel", CASES)
+def test_against_float64(shape, tile, kernel):
+    print(f"[case] {shape} T={tile} {kernel}", flush=True)
     X, W, got, plan = _spectra(shape, tile)
+    assert _tile(plan) == kernel
     ref, mag = _channel_sum(X, W, plan.nfft % 2 == 0)
     nt = plan.info.tiles
     bound = (7 * -(-shape[1] // 16) + 3) * 2.0 ** -23
@@ -79,19 +89,23 @@ def test_against_float64(shape, tile, what):
 
 
 @pytest.mark.parametrize("shape,tile", [((4, 256, 56, 56, 256, 3), 14), ((16, 64, 56, 56, 256, 5), 28),
-                                        ((2, 512, 14, 14, 128, 3), 6), ((4, 512, 28, 28, 512, 3), 6)])
+                                        ((2, 512, 14, 14, 128, 3), 6), ((4, 512, 28, 28, 512, 3), 6),
+                                        # long sums in wave groups
+                                        ((1, 1024, 28, 28, 64, 3), 6), ((1, 4096, 14, 14, 64, 3), 6),
+                                        ((4, 2048, 40, 40, 192, 3), 14)])
 @pytest.mark.parametrize("scale,mean", [(1.0, 0.0), (2.0 ** -60, 0.0), (2.0 ** 60, 0.0), (1.0, 3.0)])
 def test_no_less_precise_than_fp32(shape, tile, scale, mean, monkeypatch):
     """Its error against float64 is no larger than the fp32 matrix
     instruction's on the same spectra, at any scale of the input, and where
     every pixel is positive and the sums lean one way."""
-    def error():
+    def error(split):
         X, W, got, plan = _spectra(shape, tile, scale, mean)
+        assert plan.kernels.contract_split == split
         ref, _ = _channel_sum(X, W, True)
         d = got[:, :, :plan.info.tiles].to(torch.complex128) - ref
         return float((d / scale).abs().pow(2).sum().sqrt() / (ref / scale).abs().pow(2).sum().sqrt())
-    split = error()
+    split = error(1)
     monkeypatch.setenv("FFTSPLIT_CONTRACT_SPLIT", "0")
-    fp32 = error()
+    fp32 = error(0)
     print(f"[case] {shape} scale={scale:g} mean={mean}: split {split:.3e} fp32 {fp32:.3e}", flush=True)
     assert split <= fp32

@@ -22,10 +22,11 @@ def test_small_operands(shape, xs, ws, monkeypatch):
     # (the operands as they were rounded, in a range that float64 squares)
     ref = oracle.direct_xcorr2d(np.ldexp(x.astype(np.float64), -xs), np.ldexp(w.astype(np.float64), -ws))
 
-    def error():
+    def error(split):
         plan = fs.Plan(*shape)
+        assert plan.kernels.direct_split == split
         y = plan.direct_conv2d(torch.from_numpy(x).cuda(), plan.direct_transform_weights(torch.from_numpy(w).cuda()))
         return np.linalg.norm(np.ldexp(y.cpu().numpy().astype(np.float64), -xs - ws) - ref) / np.linalg.norm(ref)
-    split = error()
+    split = error(1)
     monkeypatch.setenv("FFTSPLIT_DIRECT_SPLIT", "0")
-    assert split <= error()
+    assert split <= error(0)
