@@ -341,10 +341,11 @@ def hbm_floor(dev, mixes, steps=20):
 
 
 def matrix_ceiling(run, con_ms, steps=20):
-    """What the fp32 matrix cores sustain for the contraction's launch: the
-    library's matrix probe (fftsplit_probe_matrix: the same grid and
-    occupancy, the same matrix operations per wave, operands in registers,
-    no memory traffic), timed like the stages, median of `steps` launches."""
+    """What the fp32 matrix cores sustain for the launch of the fp32
+    contraction kernel: the library's matrix probe (fftsplit_probe_matrix: the
+    same grid and occupancy, the same matrix operations per wave, operands in
+    registers, no memory traffic), timed like the stages, median of `steps`
+    launches."""
     import torch
     plan, i = run.plan, run.info
     sink = plan.probe_matrix()
@@ -365,16 +366,22 @@ def matrix_ceiling(run, con_ms, steps=20):
             "executed_flops": executed,
             "probe_frac_of_peak": round(executed / (probe_us * 1e-6) / 1e12 / FP32_MFMA_PEAK_TFLOPS, 4),
             "contract_vs_probe": round(probe_us / (con_ms * 1e3), 4),
+            "contract_split": plan.kernels.contract_split,
             "note": "fftsplit_probe_matrix: the fp32 contraction kernel's grid, occupancy and matrix operations per "
-                    "wave with no memory traffic; contract_vs_probe = probe time / contraction time (warm; above 1 "
-                    "where the contraction runs on the bf16 instruction)"}
+                    "wave with no memory traffic; contract_vs_probe = probe time / contraction time (warm).  Where "
+                    "contract_split is 1 the contraction runs on the bf16 instruction instead: then the two are "
+                    "different kernels, and a ratio above 1 says by how much it beats the fp32 matrix cores' time"}
 
 
-def on_split_kernel():
-    """Whether no environment variable keeps the contraction on the fp32
-    matrix instruction (the headline layer's plan then runs the bf16 one)."""
-    return not (os.environ.get("FFTSPLIT_CONTRACT_TILE") or "FFTSPLIT_CONTRACT_PREFETCH" in os.environ
-                or os.environ.get("FFTSPLIT_CONTRACT_SPLIT", "").startswith("0"))
+def contract_variant(k):
+    """The contraction kernel of a plan, from its PlanKernels, and the dense
+    rate of fp32 products (TFLOP/s) on its matrix instruction."""
+    tile = f"{k.contract_tile_m}x{k.contract_tile_n}x{k.contract_stage_k}"
+    if k.contract_split:
+        groups = f"/{k.contract_wave_groups} wave groups" if k.contract_wave_groups > 1 else ""
+        return (f"bf16 split, {k.contract_part_products} part products, {tile}/{k.contract_real_products}M"
+                f"/prefetch{k.contract_prefetch}{groups}", SPLIT_MFMA_PEAK_TFLOPS)
+    return f"{tile}/{k.contract_real_products}M/prefetch{k.contract_prefetch}", FP32_MFMA_PEAK_TFLOPS
 
 
 def stage_record(counts, fwd, con, inv):
@@ -692,9 +699,9 @@ def main():
     wtag = f"{args.config}_T{tile}_{args.mode}"
     stages["forward"]["traffic"] = load_traffic("forward", wtag)
     stages["inverse"]["traffic"] = load_traffic("inverse", wtag)
-    split = on_split_kernel()
-    con_peak = SPLIT_MFMA_PEAK_TFLOPS if split else FP32_MFMA_PEAK_TFLOPS
-    products = 4 if split else info.contract_real_products
+    kernels = run.plan.kernels
+    split, products = kernels.contract_split, kernels.contract_real_products
+    variant, con_peak = contract_variant(kernels)
     out = {
         "metric": "effective direct-conv GFLOP/s",
         "value": round(value, 1),
@@ -712,9 +719,7 @@ def main():
                                f"cout={layer.cout} k={layer.k} stride1 same",
                    "tile": info.tile, "nfft": info.nfft, "mode": args.mode, "tiles": info.tiles,
                    "bins": info.bins,
-                   "contract_variant": "bf16 split, 6 part products" if split else
-                                       f"{info.contract_tile_m}x{info.contract_tile_n}x{info.contract_stage_k}"
-                                       f"/{info.contract_real_products}M/prefetch{info.contract_prefetch}"},
+                   "contract_variant": variant},
         "images_per_s": round(layer.n / (ms_per_step * 1e-3), 1),
         "settle_s": round(settle_s, 3),
         "settle_steps": settle_n,
