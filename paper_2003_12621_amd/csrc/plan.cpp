@@ -172,6 +172,13 @@ static void choose_forward_band(fftsplit_plan_s& p) {
     p.fwd_lds = int(lds);
 }
 
+// FFTSPLIT_CONTRACT_PREFETCH, or 0 where it is not set to 1..3.
+static int prefetch_env() {
+    const char* e = std::getenv("FFTSPLIT_CONTRACT_PREFETCH");
+    const int pf = e ? std::atoi(e) : 0;
+    return pf >= 1 && pf <= 3 ? pf : 0;
+}
+
 static std::string contract_name(const fftsplit_plan_s& p) {
     if (!p.con_split) return "fp32";
     const SplitTileShape& v = kSplitTileShapes[p.con_split];
@@ -215,7 +222,7 @@ static void choose_contract_split(fftsplit_plan_s& p) {
     p.con_split = kSplitNone;
     const char* off = std::getenv("FFTSPLIT_CONTRACT_SPLIT");
     const char* tile = std::getenv("FFTSPLIT_CONTRACT_TILE");
-    if ((off && *off == '0') || (tile && *tile) || std::getenv("FFTSPLIT_CONTRACT_PREFETCH")) return;
+    if ((off && *off == '0') || (tile && *tile) || prefetch_env()) return;
     const auto blocks = [&](int bm, int bn) {
         return p.coutp % bm == 0 && p.ntp % bn == 0 ? size_t(p.coutp / bm) * size_t(p.ntp / bn) * size_t(p.bins) : size_t(0);
     };
@@ -424,7 +431,6 @@ static fftsplit_status_t build_plan(const fftsplit_problem_t* prob, int device, 
         plan->con_kc = 8;
         plan->con_prefetch = 3;
     }
-    const char* pf_env = std::getenv("FFTSPLIT_CONTRACT_PREFETCH");
     if (const char* v = std::getenv("FFTSPLIT_CONTRACT_TILE")) {
         if (*v) {
             plan->con_prefetch = 2;
@@ -448,10 +454,7 @@ static fftsplit_status_t build_plan(const fftsplit_problem_t* prob, int device, 
             plan->con_products = prod;
         }
     }
-    if (pf_env) {
-        const int pf = std::atoi(pf_env);
-        if (pf >= 1 && pf <= 3) plan->con_prefetch = pf;
-    }
+    if (const int pf = prefetch_env()) plan->con_prefetch = pf;
     // the LDS-prefetch variants exist for the 3-product tiles with
     // 16-channel stages (64x64, 128x32, 128x64, 64x128; three stages ahead
     // for 64x64 only) and for 64x64 with 8-channel stages

@@ -63,6 +63,12 @@ def test_fp32_contraction_is_reported_as_such(monkeypatch):
     assert fields(plan(headline, 28)) == (0, 1, True)
 
 
+@pytest.mark.parametrize("value,split", [("", 1), ("0", 1), ("7", 1), ("1", 0), ("3", 0)])
+def test_prefetch_variable_that_asks_for_nothing(value, split, monkeypatch):
+    monkeypatch.setenv("FFTSPLIT_CONTRACT_PREFETCH", value)
+    assert plan((16, 256, 56, 56, 256, 5), 28).kernels.contract_split == split
+
+
 def test_null_arguments():
     assert fs.lib().fftsplit_plan_kernels(None, ctypes.byref(fs.PlanKernels())) == fs.ERROR_INVALID_VALUE
     assert fs.lib().fftsplit_plan_kernels(plan((1, 3, 32, 32, 16, 3), 6)._h, None) == fs.ERROR_INVALID_VALUE
