@@ -134,7 +134,9 @@ typedef struct {
     size_t workspace_bytes;
     size_t xspec_offset, xspec_bytes;
     size_t yspec_offset, yspec_bytes;
-    size_t aux_offset, aux_bytes;   /* overlap-add seam partials (0 for overlap-save) */
+    size_t aux_offset, aux_bytes;   /* overlap-add seam partials, room for a patch's whole
+                                     * L x L result each, of which the inverse uses at most
+                                     * the seams (0 for overlap-save) */
     /* The contraction on the fp32 matrix instruction: output tile
      * contract_tile_m channels x contract_tile_n patches, input channels in
      * stages of contract_stage_k, and 3 (Gauss) or 4 real matrix products
@@ -244,6 +246,10 @@ typedef struct {
      * of 64 pixels that are direct_block_w wide; 0 (and 0) if on the fp32 one,
      * in runs of pixels. */
     int direct_split, direct_block_w;
+    /* The OaAConv configuration's inverse: patch rows (of one plane) and images
+     * whose results a workgroup adds up in LDS; 0 and 0 where they go through
+     * the aux buffer (planes too wide) and for other configurations. */
+    int oaaconv_strip_rows, oaaconv_strip_images;
 } fftsplit_plan_kernels_t;
 
 /* Fails with FFTSPLIT_ERROR_INVALID_VALUE on a NULL argument. */

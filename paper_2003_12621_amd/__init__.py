@@ -69,7 +69,7 @@ class PlanKernels(ctypes.Structure):
     _fields_ = [(f, ctypes.c_int) for f in
                 ("contract_split", "contract_tile_m", "contract_tile_n", "contract_stage_k", "contract_prefetch",
                  "contract_wave_groups", "contract_real_products", "contract_part_products", "direct_split",
-                 "direct_block_w")]
+                 "direct_block_w", "oaaconv_strip_rows", "oaaconv_strip_images")]
 
 
 class FftsplitError(RuntimeError):

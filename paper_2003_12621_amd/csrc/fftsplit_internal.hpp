@@ -10,6 +10,21 @@
 
 #define FFTSPLIT_EXPORT extern "C" __attribute__((visibility("default")))
 
+namespace fftsplit {
+
+// How the OaAConv inverse that adds results up in LDS divides the planes
+// (k_oaa.hip, choose_oaa_strips in plan.cpp).
+struct OaaStrips {
+    int blocks;            // workgroups, or 0: through memory instead
+    int R;                 // owned patch rows per workgroup
+    int strips;            // per plane
+    int ni;                // images per workgroup (1 unless strips == 1)
+    int lds;               // bytes
+    int threads, passes;   // patches are taken threads at a time
+};
+
+}  // namespace fftsplit
+
 struct fftsplit_plan_s {
     fftsplit_problem_t prob;
     int device;                 // HIP ordinal, or -1 for an architecture-only plan
@@ -32,6 +47,7 @@ struct fftsplit_plan_s {
     // direct convolution on the bf16 instruction (k_direct.hip): log2 of the
     // width of its 64-pixel blocks, or 0 where the fp32 kernel runs
     int dir_ltw;
+    fftsplit::OaaStrips oaa_strips;
     // overlap-save band variant of the forward transform (band.hpp):
     // used if fwd_band; LDS row pitch, left zero columns, zero-row slot and
     // dynamic LDS bytes; fwd_sweep: items a grid apart instead of a

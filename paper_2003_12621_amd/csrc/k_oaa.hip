@@ -24,8 +24,6 @@
 // in LDS; for images too wide for its strips oaa_inverse_kernel writes them
 // to the aux buffer and the seam pass sums the 1-4 contributions of every
 // pixel.
-#include <algorithm>
-#include <climits>
 #include <type_traits>
 
 #include "fftsplit_internal.hpp"
@@ -248,14 +246,6 @@ __global__ __launch_bounds__(256) void oaa_inverse_kernel(const float2* __restri
 // us (244 MB, 4.7 TB/s); 32x64x224^2 -> 64 K = 3 865 + 615 against 346 us,
 // 32x512x14^2 K = 3 25 + 47 against 14 us, 1x64x224^2 K = 3 20 + 17 against
 // 13 us, 8x64x56^2 K = 7 20 + 10 against 17 us.
-struct OaaStrip {
-    int R;        // owned patch rows per workgroup
-    int strips;   // per plane
-    int ni;       // images per workgroup (1 unless strips == 1)
-    int lds;      // bytes
-    int threads, passes;   // patches are taken threads at a time
-};
-
 template <int L>
 __global__ __launch_bounds__(256) void oaa_inverse_strip_kernel(const float2* __restrict__ ys,
                                                                 const float* __restrict__ bias,
@@ -374,38 +364,6 @@ __global__ __launch_bounds__(256) void oaa_inverse_strip_kernel(const float2* __
     }
 }
 
-// The strips of a plan, or R = 0 where even kMinRows patch rows exceed the
-// LDS of a launch without special attributes (64 KB: images of more than
-// about 700 (K = 3) to 360 (K = 7) columns): those go through memory.
-// A strip reads (R + 2) / R of its spectra, so it is as tall as 40 KB of LDS
-// (four workgroups per CU) and 1024 workgroups allow, and not below kMinRows.
-static OaaStrip oaa_strips(const fftsplit_plan_s& p) {
-    constexpr int kMinRows = 4, kLds = 40 * 1024, kMaxLds = 64 * 1024;
-    const int T = p.T, P = p.P;
-    const long long planes = (long long)p.prob.n * p.prob.cout;
-    const size_t pitch = size_t(p.tw * T + 2 * P) | 1;
-    auto bytes = [&](int R) { return (size_t(R) * T + 2 * P) * pitch * 4; };
-    OaaStrip s{};
-    int R = p.th;
-    while (R > kMinRows && (bytes(R) > kLds || planes * ((p.th + R - 1) / R) < 1024)) --R;
-    if (bytes(R) > kMaxLds) return s;
-    s.strips = (p.th + R - 1) / R;
-    s.R = R = (p.th + s.strips - 1) / s.strips;
-    s.ni = 1;
-    int patches = (s.strips == 1 ? R : std::min(p.th, R + 2)) * p.tw;
-    if (s.strips == 1) {
-        // small planes: more images per workgroup while the launch still fills the chip
-        while (s.ni < p.prob.n && (s.ni + 1) * patches <= 256 && (s.ni + 1) * bytes(R) <= size_t(kLds) &&
-               planes / (s.ni + 1) >= 1024)
-            ++s.ni;
-        patches *= s.ni;
-    }
-    s.lds = int(s.ni * bytes(R));
-    s.passes = (patches + 255) / 256;
-    s.threads = ((patches + s.passes - 1) / s.passes + 63) / 64 * 64;
-    return s;
-}
-
 template <int L>
 static hipError_t launch_oaa_forward_L(const fftsplit_plan_s& p, const float* x, float2* xs, hipStream_t s,
                                        const LaunchEvents& ev) {
@@ -417,11 +375,9 @@ static hipError_t launch_oaa_forward_L(const fftsplit_plan_s& p, const float* x,
 template <int L>
 static hipError_t launch_oaa_inverse_L(const fftsplit_plan_s& p, const float2* ys, const float* bias, float* y,
                                        float* aux, hipStream_t s, const LaunchEvents& ev) {
-    const OaaStrip st = oaa_strips(p);
-    const long long blocks = (long long)p.prob.cout * ((p.prob.n + std::max(st.ni, 1) - 1) / std::max(st.ni, 1)) *
-                             std::max(st.strips, 1);
-    if (st.R && blocks <= INT_MAX)
-        return launch_kernel(oaa_inverse_strip_kernel<L>, dim3(unsigned(blocks)), dim3(unsigned(st.threads)),
+    const OaaStrips& st = p.oaa_strips;
+    if (st.blocks)
+        return launch_kernel(oaa_inverse_strip_kernel<L>, dim3(unsigned(st.blocks)), dim3(unsigned(st.threads)),
                              unsigned(st.lds), s, ev.start, ev.stop, ys, bias, y, p.prob.n, p.prob.cout, p.prob.h,
                              p.prob.w, p.th, p.tw, p.ntp, int(p.relu), st.R, st.strips, st.ni, st.passes);
     const dim3 grid(unsigned((p.nt + 255) / 256), unsigned(p.prob.cout));

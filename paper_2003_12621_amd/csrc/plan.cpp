@@ -6,6 +6,7 @@
 // (8, 16, 32), so T = L - K + 1, and a plan without an explicit tile picks
 // the L whose modelled time (streamed bytes at an effective bandwidth plus
 // contraction flops at an effective matrix-core rate) is smallest.
+#include <algorithm>
 #include <cerrno>
 #include <cstdint>
 #include <climits>
@@ -170,6 +171,44 @@ static void choose_forward_band(fftsplit_plan_s& p) {
     p.fwd_co = co;
     p.fwd_zslot = slots;
     p.fwd_lds = int(lds);
+}
+
+// The strips of the OaAConv inverse.  None where even kMinRows patch rows exceed
+// the LDS of a launch without special attributes (64 KB: from four patch rows
+// on, images of more than 1167, 675 and 469 columns at K = 3, 5, 7): those
+// planes go through memory.  A strip reads (R + 2) / R of its spectra, so it is
+// as tall as 40 KB of LDS (four workgroups per CU) and 1024 workgroups allow,
+// and not below kMinRows.
+static void choose_oaa_strips(fftsplit_plan_s& p) {
+    constexpr int kMinRows = 4, kLds = 40 * 1024, kMaxLds = 64 * 1024;
+    p.oaa_strips = OaaStrips{};
+    if (p.L % 2 == 0) return;
+    const int T = p.T, P = p.P;
+    const long long planes = (long long)p.prob.n * p.prob.cout;
+    const size_t pitch = size_t(p.tw * T + 2 * P) | 1;
+    const auto bytes = [&](int R) { return (size_t(R) * T + 2 * P) * pitch * 4; };
+    OaaStrips s{};
+    int R = p.th;
+    while (R > kMinRows && (bytes(R) > kLds || planes * ((p.th + R - 1) / R) < 1024)) --R;
+    if (bytes(R) > kMaxLds) return;
+    s.strips = (p.th + R - 1) / R;
+    s.R = R = (p.th + s.strips - 1) / s.strips;
+    s.ni = 1;
+    int patches = (s.strips == 1 ? R : std::min(p.th, R + 2)) * p.tw;
+    if (s.strips == 1) {
+        // small planes: more images per workgroup while the launch still fills the chip
+        while (s.ni < p.prob.n && (s.ni + 1) * patches <= 256 && (s.ni + 1) * bytes(R) <= size_t(kLds) &&
+               planes / (s.ni + 1) >= 1024)
+            ++s.ni;
+        patches *= s.ni;
+    }
+    const long long blocks = (long long)p.prob.cout * ((p.prob.n + s.ni - 1) / s.ni) * s.strips;
+    if (blocks > INT_MAX) return;
+    s.blocks = int(blocks);
+    s.lds = int(s.ni * bytes(R));
+    s.passes = (patches + 255) / 256;
+    s.threads = ((patches + s.passes - 1) / s.passes + 63) / 64 * 64;
+    p.oaa_strips = s;
 }
 
 // FFTSPLIT_CONTRACT_PREFETCH, or 0 where it is not set to 1..3.
@@ -478,6 +517,7 @@ static fftsplit_status_t build_plan(const fftsplit_problem_t* prob, int device, 
 
     choose_contract_split(*plan);
     choose_direct(*plan);
+    choose_oaa_strips(*plan);
     choose_forward_band(*plan);
     choose_inverse_band(*plan);
     // The max-pool goes into the overlap-save inverse's store phase when no
@@ -597,6 +637,8 @@ FFTSPLIT_EXPORT fftsplit_status_t fftsplit_plan_kernels(fftsplit_plan_t plan, ff
         k.direct_split = 1;
         k.direct_block_w = 1 << plan->dir_ltw;
     }
+    k.oaaconv_strip_rows = plan->oaa_strips.R;
+    k.oaaconv_strip_images = plan->oaa_strips.ni;
     *out = k;
     return FFTSPLIT_SUCCESS;
 }

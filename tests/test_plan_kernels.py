@@ -13,6 +13,7 @@ import paper_2003_12621_amd as fs
 from test_abi_host import HEADER, ROOT
 from test_gpu_contract_split import CASES, _tile
 from test_gpu_direct_split import CASES as DIRECT_CASES
+from test_gpu_oaa_strip import CASES as STRIP_CASES
 
 
 def plan(shape, tile=0):
@@ -67,6 +68,20 @@ def test_fp32_contraction_is_reported_as_such(monkeypatch):
 def test_prefetch_variable_that_asks_for_nothing(value, split, monkeypatch):
     monkeypatch.setenv("FFTSPLIT_CONTRACT_PREFETCH", value)
     assert plan((16, 256, 56, 56, 256, 5), 28).kernels.contract_split == split
+
+
+@pytest.mark.parametrize("shape,strip", STRIP_CASES)
+def test_oaaconv_strips(shape, strip):
+    k = plan(shape, shape[5]).kernels
+    assert (k.oaaconv_strip_rows, k.oaaconv_strip_images) == strip
+
+
+@pytest.mark.parametrize("k,widest", [(3, 1167), (5, 675), (7, 469)])
+def test_oaaconv_strip_limit(k, widest):
+    """Four patch rows of an image fit a strip up to this many columns."""
+    rows = [plan((1, 1, 8 * k, w, 2, k), k).kernels.oaaconv_strip_rows for w in range(8, widest + 200, 3)]
+    rows += [plan((1, 1, 8 * k, w, 2, k), k).kernels.oaaconv_strip_rows for w in (widest, widest + 1)]
+    assert [bool(r) for r in rows] == [w <= widest for w in [*range(8, widest + 200, 3), widest, widest + 1]]
 
 
 def test_null_arguments():
