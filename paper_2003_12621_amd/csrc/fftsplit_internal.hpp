@@ -75,18 +75,17 @@ struct fftsplit_plan_s {
 
 namespace fftsplit {
 
-// Tiles of the bf16-split contraction: channels x patches, stages loaded ahead
-// (a2: two) and wave groups that share the reduction (gN).
+// Tiles of the bf16-split contraction: channels x patches, and wave groups that
+// share the reduction (gN).
 enum SplitTile {
-    kSplitNone = 0, kSplit128x128, kSplit256x64, kSplit64x256, kSplit128x64, kSplit64x64, kSplit64x64a2,
-    kSplit64x64g2, kSplit64x32g2, kSplit64x32g4
+    kSplitNone = 0, kSplit128x128, kSplit256x64, kSplit64x256, kSplit128x64, kSplit64x64, kSplit64x64g2,
+    kSplit64x32g2, kSplit64x32g4
 };
 struct SplitTileShape {
-    int bm, bn, ahead, groups;
+    int bm, bn, groups;
 };
-constexpr SplitTileShape kSplitTileShapes[] = {
-    {0, 0, 0, 0},    {128, 128, 1, 1}, {256, 64, 1, 1}, {64, 256, 1, 1}, {128, 64, 1, 1},
-    {64, 64, 1, 1},  {64, 64, 2, 1},   {64, 64, 1, 2},  {64, 32, 1, 2},  {64, 32, 1, 4}};
+constexpr SplitTileShape kSplitTileShapes[] = {{0, 0, 0},   {128, 128, 1}, {256, 64, 1}, {64, 256, 1}, {128, 64, 1},
+                                               {64, 64, 1}, {64, 64, 2},   {64, 32, 2},  {64, 32, 4}};
 
 // Granularity of the contraction's output tiles (patches x channels).
 constexpr int kTileGranule = 64;

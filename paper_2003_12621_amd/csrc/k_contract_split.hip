@@ -32,7 +32,7 @@
 // blocks and an output row is written in 16-byte pairs of patches.
 //
 // A workgroup tile is BM channels x BN patches of one bin, wave tiles of
-// 16 TM x 16 TN; channel blocks are loaded PF ahead straight into LDS as
+// 16 TM x 16 TN; channel blocks are loaded one ahead straight into LDS as
 // fp32 and split after the LDS read.  At 64 x 64 a wave issues 464 vector
 // instructions of splits, 64 of them for the scale (and 128 additions where a block is summed from zero)
 // beside 384 matrix instructions of 16 cycles per channel block, which two
@@ -53,8 +53,8 @@
 //     32x64x224^2, 8192 patches           283 -> 240  (4.5 TB/s)
 //     1x512x28^2 at L = 8, 25 patches      34 ->  22
 // Tried without gain: the vector work interleaved with the matrix
-// instructions by the scheduler instead of two waves overlapping, three stages
-// ahead, and a priority for one of a compute unit's two workgroups.
+// instructions by the scheduler instead of two waves overlapping, two and three
+// stages ahead, and a priority for one of a compute unit's two workgroups.
 #include "bf16_split.hpp"
 #include "fftsplit_internal.hpp"
 #include "launch_util.hpp"
@@ -63,24 +63,11 @@
 
 namespace fftsplit {
 
-// Waits until at most N vector memory instructions and no LDS read are
-// outstanding, then passes the workgroup's barrier.  One block, so that
-// nothing the wave reads from LDS before it can still be in flight after it.
-template <int N>
+// Waits until no vector memory instruction and no LDS read is outstanding, then
+// passes the workgroup's barrier.  One block, so that nothing the wave reads
+// from LDS before it can still be in flight after it.
 __device__ __forceinline__ void wait_and_barrier() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-
-// wait_and_barrier for n (<= MAX) later stages of LPS loads in flight.
-template <int MAX, int LPS>
-__device__ __forceinline__ void wait_stages(int n) {
-    static_assert(MAX * LPS < 64, "the counter's range");
-    if constexpr (MAX <= 0) {
-        wait_and_barrier<0>();
-    } else {
-        if (n >= MAX) wait_and_barrier<MAX * LPS>();
-        else wait_stages<MAX - 1, LPS>(n);
-    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // 16 bytes per lane from uniform base + lane offset straight into LDS: lane
@@ -147,14 +134,14 @@ struct SplitShape {
     static_assert(NT % (BM / 2) == 0 && NT % (BN / 2) == 0, "whole rows per load");
 };
 
-template <int BM, int BN, int TM, int TN, int PF, int KG, bool WS, bool XS>
+template <int BM, int BN, int TM, int TN, int KG, bool WS, bool XS>
 __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void contract_split_kernel(
     const float2* __restrict__ xs, const float2* __restrict__ ws, float2* __restrict__ ys, int cin, int coutp, int ntp,
     int nt, int nbco, int nbt, int nbins, int ygroup, int npacked) {
     using S = SplitShape<BM, BN, TM, TN>;
     constexpr int KC = S::KC;
     constexpr int NT = S::NT;             // threads of a group
-    extern __shared__ float4 lds_raw[];   // PF + 1 stage buffers for each group
+    extern __shared__ float4 lds_raw[];   // two stage buffers for each group
 
     const int group = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(int(threadIdx.x) / NT);
     const int tid = int(threadIdx.x) - group * NT;
@@ -186,7 +173,7 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
     const uint64_t xbase = uniform_address(xs + spec_offset(0, f, t0, nbins, ntp));
     const uint64_t xblock = uint64_t(unsigned(nbins)) * xrow;   // bytes from a channel block to the next, per channel
 
-    float2* const lds = reinterpret_cast<float2*>(lds_raw) + group * ((PF + 1) * S::STAGE);
+    float2* const lds = reinterpret_cast<float2*>(lds_raw) + group * (2 * S::STAGE);
     // Channel block s into `stage`.  In a partial last one the missing rows
     // are read from the last row (in range); the filter's are zeroed before
     // they are used (below), so that what the patch rows hold does not count.
@@ -278,12 +265,10 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
         }
     };
 
-    constexpr int NB = PF + 1;
-    constexpr int LPS = S::WL + S::XL;   // memory instructions per stage and thread
     // (a block of padding patches only has zero spectra: no stages)
     const int nstage = t0 < nt ? (cin + KC - 1) / KC : 0;
     // The group's stage of iteration it (channel block it * KG + group).
-    auto buffer = [&](int it) __attribute__((always_inline)) { return lds + (NB == 2 ? it & 1 : it % NB) * S::STAGE; };
+    auto buffer = [&](int it) __attribute__((always_inline)) { return lds + (it & 1) * S::STAGE; };
     auto load_stage = [&](int it) __attribute__((always_inline)) {
         const int s = it * KG + group;
         if (s < nstage) dma_stage(s, buffer(it));
@@ -298,18 +283,16 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
 #pragma unroll
                 for (int r = 0; r < 4; ++r) accR[i][j][r] = accI[i][j][r] = 0.f;
 
-#pragma unroll
-        for (int d = 0; d < PF; ++d) load_stage(d);
+        load_stage(0);
         const int nit = (nstage + KG - 1) / KG;
         auto iterations = [&](int it, int end, auto fresh) __attribute__((always_inline)) {
             for (; it < end; ++it) {
-                // this iteration's stage is there once at most the loads of
-                // the group's stages issued after it remain; past the barrier
-                // every wave has also finished with the buffer of the
-                // iteration before, which iteration it + PF then fills
+                // past the wait and the barrier this iteration's stage is
+                // there, and every wave has finished with the buffer of the
+                // iteration before, which the next one's stage then fills
                 const int s = it * KG + group;
-                wait_stages<PF - 1, LPS>(s < nstage ? min(PF - 1, (nstage - 1 - s) / KG) : 0);
-                load_stage(it + PF);
+                wait_and_barrier();
+                load_stage(it + 1);
                 float2* const cur = buffer(it);
                 if (it == nit - 1 && cin % KC != 0) {
                     // the partial block's missing filter rows (only its own
@@ -418,9 +401,9 @@ template <SplitTile TILE, int TM, int TN>
 static hipError_t launch_split_v(const fftsplit_plan_s& p, const float2* xs, const float2* ws, float2* ys,
                                  hipStream_t s, const LaunchEvents& ev) {
     constexpr SplitTileShape V = kSplitTileShapes[TILE];
-    constexpr int BM = V.bm, BN = V.bn, PF = V.ahead, KG = V.groups;
+    constexpr int BM = V.bm, BN = V.bn, KG = V.groups;
     using S = SplitShape<BM, BN, TM, TN>;
-    constexpr int lds = KG * (PF + 1) * S::STAGE * 8;
+    constexpr int lds = KG * 2 * S::STAGE * 8;
     static_assert(lds <= 160 * 1024 && (KG - 1) * 2 * TM * TN * S::NT * 16 <= lds, "fits the LDS");
     if (p.coutp % BM != 0 || p.ntp % BN != 0) return hipErrorInvalidValue;
     const int nbco = p.coutp / BM, nbt = p.ntp / BN;
@@ -435,10 +418,10 @@ static hipError_t launch_split_v(const fftsplit_plan_s& p, const float2* xs, con
     // 416; 2x256x112^2 77.7, 78.7.  (blocks of padding patches read nothing)
     const int readers = (p.nt + BN - 1) / BN;
     const bool w_stream = readers <= (BM * BN <= 64 * 64 ? 1 : 2);
-    auto kern = w_stream ? (nbco == 1 ? contract_split_kernel<BM, BN, TM, TN, PF, KG, true, true>
-                                      : contract_split_kernel<BM, BN, TM, TN, PF, KG, true, false>)
-                         : (nbco == 1 ? contract_split_kernel<BM, BN, TM, TN, PF, KG, false, true>
-                                      : contract_split_kernel<BM, BN, TM, TN, PF, KG, false, false>);
+    auto kern = w_stream ? (nbco == 1 ? contract_split_kernel<BM, BN, TM, TN, KG, true, true>
+                                      : contract_split_kernel<BM, BN, TM, TN, KG, true, false>)
+                         : (nbco == 1 ? contract_split_kernel<BM, BN, TM, TN, KG, false, true>
+                                      : contract_split_kernel<BM, BN, TM, TN, KG, false, false>);
     const hipError_t attr = allow_dynamic_lds(kern, lds);
     if (attr != hipSuccess) return attr;
     const size_t nb = size_t(nbco) * nbt * p.bins;
@@ -454,7 +437,6 @@ hipError_t launch_contract_split(const fftsplit_plan_s& p, const float2* xs, con
         case kSplit64x256: return launch_split_v<kSplit64x256, 4, 4>(p, xs, ws, ys, s, ev);
         case kSplit128x64: return launch_split_v<kSplit128x64, 4, 2>(p, xs, ws, ys, s, ev);
         case kSplit64x64: return launch_split_v<kSplit64x64, 2, 2>(p, xs, ws, ys, s, ev);
-        case kSplit64x64a2: return launch_split_v<kSplit64x64a2, 2, 2>(p, xs, ws, ys, s, ev);
         case kSplit64x64g2: return launch_split_v<kSplit64x64g2, 2, 2>(p, xs, ws, ys, s, ev);
         case kSplit64x32g2: return launch_split_v<kSplit64x32g2, 2, 2>(p, xs, ws, ys, s, ev);
         case kSplit64x32g4: return launch_split_v<kSplit64x32g4, 2, 2>(p, xs, ws, ys, s, ev);

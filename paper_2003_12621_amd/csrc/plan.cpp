@@ -222,7 +222,6 @@ static std::string contract_name(const fftsplit_plan_s& p) {
     if (!p.con_split) return "fp32";
     const SplitTileShape& v = kSplitTileShapes[p.con_split];
     std::string name = "split " + std::to_string(v.bm) + "x" + std::to_string(v.bn);
-    if (v.ahead > 1) name += " +" + std::to_string(v.ahead);
     if (v.groups > 1) name += "/" + std::to_string(v.groups);
     return name;
 }
@@ -244,17 +243,24 @@ static std::string contract_name(const fftsplit_plan_s& p) {
 // L = 8, 25 patches: 24, 64x64 in two groups 31), or in two with fewer than
 // 16 blocks (the whole 10x64x12^2 K=5 -> 8 layer: 14.7, 64x64 16.3; 1x99x12^2
 // K=1 -> 484: 21.9, four groups 24.3).
-// Patches padded to 32 only stay on the fp32 kernel's 128x32 tiles: there the
-// filter spectra's stream is what takes the time (300 MB in 65 us on
-// 32x512x14^2), and split 128x32 tiles, 63-68 us, made the whole layer 80-89 us
-// against 81-84 on different boards.  Three or four whole channel blocks in a grid of at most three workgroups a
+// Patches padded to an odd multiple of 32 stay on the fp32 kernel's 128x32
+// tiles.  With one such block the filter spectra's stream is what takes the
+// time (300 MB in 65 us on 32x512x14^2), and split 128x32 tiles, 63-68 us, made
+// the whole layer 80-89 us against 81-84 on different boards.  With more blocks
+// (16x256x56^2 K = 5 at T = 12: 400 patches, padded to 416) it is only that no
+// split tile divides them; padding those to 64 has not been measured.
+// Three or four whole channel blocks in a grid of at most three workgroups a
 // compute unit stay on the fp32 kernel, whose whole sum is loaded at once and
-// whose waves have the shorter chain (the whole 1x64x224^2 layer: 28.8 us,
-// 64x64 split 29.3).
-// The single-group 64x64 tile loads two stages ahead (three workgroups on a
-// compute unit) where there are more than four to load or the grid is no larger
-// than that, one ahead (four workgroups) otherwise: the whole 11x119x182x55 ->
-// 24 layer 69.8 us, two ahead 71.8.
+// whose waves have the shorter chain: contraction fp32 and split 64x64
+// 1x64x112^2 -> 128 8.8, 9.6 us; 2x64x112^2 8.9, 9.6; 1x64x224^2 13.7, 13.9.
+// The line is drawn at four blocks and small grids: 1x48x224^2 11.9, 11.8; 2x48x
+// 100^2 -> 96 11.9, 11.5; 1x64x224^2 at T = 6, 736 workgroups, 17.7, 16.6.
+// Every tile loads one stage ahead.  Two ahead, 64x64 tiles hold three
+// workgroups on a compute unit instead of four: whole layers one and two ahead
+// 5x83x56^2 -> 192 37.4, 38.2 us; 1x99x230^2 -> 60 47.3, 49.1; 10x23x112^2 ->
+// 70 48.4, 49.9; 3x256x128^2 -> 64 77.1, 78.2; 2x20x56^2 -> 64 18.8, 18.5;
+// 1x300x200^2 -> 192 at T = 30, which is bound by the filters' stream, 155.1,
+// 152.6.
 // An explicit FFTSPLIT_CONTRACT_TILE or _PREFETCH, or
 // FFTSPLIT_CONTRACT_SPLIT=0, selects the fp32 kernel instead.
 static void choose_contract_split(fftsplit_plan_s& p) {
@@ -277,8 +283,6 @@ static void choose_contract_split(fftsplit_plan_s& p) {
     else if (p.prob.cin <= 4 * kChanBlock && p.prob.cin % kChanBlock == 0 && blocks(64, 64) <= size_t(3) * p.cus) return;
     else if (p.prob.cin <= 4 * kChanBlock || blocks(64, 64) > kFull) p.con_split = kSplit64x64;
     else p.con_split = kSplit64x64g2;
-    if (p.con_split == kSplit64x64 && (p.prob.cin > 4 * kChanBlock || blocks(64, 64) <= size_t(3) * p.cus))
-        p.con_split = kSplit64x64a2;
 }
 
 // The direct convolution's kernel.  The bf16 one takes 32 input channels a
@@ -620,7 +624,7 @@ FFTSPLIT_EXPORT fftsplit_status_t fftsplit_plan_kernels(fftsplit_plan_t plan, ff
         k.contract_tile_m = v.bm;
         k.contract_tile_n = v.bn;
         k.contract_stage_k = kChanBlock;
-        k.contract_prefetch = v.ahead;
+        k.contract_prefetch = 1;
         k.contract_wave_groups = v.groups;
         k.contract_real_products = 4;
         k.contract_part_products = 6;

@@ -23,33 +23,33 @@ fs = pytest.importorskip("paper_2003_12621_amd")
 pytestmark = pytest.mark.gpu
 
 # (n, cin, h, w, cout, k), tile T, then what the plan's rule gives: channels x
-# patches of the workgroup tile, stages loaded ahead, wave groups
+# patches of the workgroup tile, wave groups
 CASES = [
-    ((2, 97, 24, 24, 70, 3), 6, (64, 32, 1, 2)),      # a partial block
-    ((3, 80, 24, 24, 40, 3), 6, (64, 32, 1, 2)),      # five channel blocks
-    ((1, 270, 24, 24, 70, 3), 6, (64, 32, 1, 4)),     # a partial block
-    ((3, 256, 24, 24, 40, 3), 6, (64, 32, 1, 4)),
-    ((1, 3, 20, 40, 5, 3), 14, (64, 64, 2, 1)),       # one channel block, padding patches
-    ((20, 50, 56, 56, 40, 3), 14, (64, 64, 2, 1)),    # a partial block
-    ((1, 1, 30, 30, 1, 3), 30, (64, 64, 2, 1)),       # one channel
-    ((5, 83, 56, 56, 192, 3), 14, (64, 64, 2, 1)),    # many blocks
-    ((10, 23, 112, 112, 70, 3), 14, (64, 64, 1, 1)),  # two blocks, one of them partial
-    ((30, 50, 56, 56, 40, 3), 14, (64, 64, 1, 1)),    # four blocks
-    ((3, 83, 56, 56, 192, 3), 14, (64, 64, 1, 2)),    # a partial block
-    ((4, 96, 56, 40, 192, 3), 14, (64, 64, 1, 2)),    # even blocks
-    ((4, 37, 100, 100, 128, 3), 30, (128, 64, 1, 1)),
-    ((4, 47, 100, 100, 256, 3), 30, (256, 64, 1, 1)),
-    ((8, 35, 110, 120, 128, 3), 30, (128, 128, 1, 1)),
-    ((16, 34, 112, 100, 48, 3), 30, (64, 256, 1, 1)),
-    ((2, 18, 25, 25, 20, 5), 5, (64, 64, 2, 1)),      # odd transform size: no packed bins
-    ((2, 70, 25, 25, 20, 5), 5, (64, 32, 1, 2)),      # odd transform size
+    ((2, 97, 24, 24, 70, 3), 6, (64, 32, 2)),      # a partial block
+    ((3, 80, 24, 24, 40, 3), 6, (64, 32, 2)),      # five channel blocks
+    ((1, 270, 24, 24, 70, 3), 6, (64, 32, 4)),     # a partial block
+    ((3, 256, 24, 24, 40, 3), 6, (64, 32, 4)),
+    ((1, 3, 20, 40, 5, 3), 14, (64, 64, 1)),       # one channel block, padding patches
+    ((20, 50, 56, 56, 40, 3), 14, (64, 64, 1)),    # a partial block
+    ((1, 1, 30, 30, 1, 3), 30, (64, 64, 1)),       # one channel
+    ((5, 83, 56, 56, 192, 3), 14, (64, 64, 1)),    # many blocks
+    ((10, 23, 112, 112, 70, 3), 14, (64, 64, 1)),  # two blocks, one of them partial
+    ((30, 50, 56, 56, 40, 3), 14, (64, 64, 1)),    # four blocks
+    ((3, 83, 56, 56, 192, 3), 14, (64, 64, 2)),    # a partial block
+    ((4, 96, 56, 40, 192, 3), 14, (64, 64, 2)),    # even blocks
+    ((4, 37, 100, 100, 128, 3), 30, (128, 64, 1)),
+    ((4, 47, 100, 100, 256, 3), 30, (256, 64, 1)),
+    ((8, 35, 110, 120, 128, 3), 30, (128, 128, 1)),
+    ((16, 34, 112, 100, 48, 3), 30, (64, 256, 1)),
+    ((2, 18, 25, 25, 20, 5), 5, (64, 64, 1)),      # odd transform size: no packed bins
+    ((2, 70, 25, 25, 20, 5), 5, (64, 32, 2)),      # odd transform size
 ]
 
 
 def _tile(plan):
     k = plan.kernels
     assert k.contract_split
-    return k.contract_tile_m, k.contract_tile_n, k.contract_prefetch, k.contract_wave_groups
+    return k.contract_tile_m, k.contract_tile_n, k.contract_wave_groups
 
 
 def _spectra(shape, tile, scale=1.0, mean=0.0):
