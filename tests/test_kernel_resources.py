@@ -26,8 +26,27 @@ BUDGETS = [
     # three 48 KB workgroups of four waves per CU: three waves per SIMD
     ("k_contract.o", r"contract_kernelILi64ELi64ELi16ELi2ELb1ELi2E", 168),
     ("k_contract.o", r"contract_kernelILi128ELi32ELi16ELi4ELb1ELi2E", 168),
-    # 8-channel stages three ahead: four 32 KB workgroups per CU, four waves per SIMD
+    # 8-channel stages three ahead: four 32 KB workgroups per CU, four waves per
+    # SIMD (runs where FFTSPLIT_CONTRACT_SPLIT=0 keeps large grids on this kernel)
     ("k_contract.o", r"contract_kernelILi64ELi64ELi8ELi2ELb1ELi3E", 128),
+    # 64 x 64 wave tiles: two waves per SIMD
+    ("k_contract_split.o", r"contract_split_kernelILi128ELi128ELi4ELi4ELi1E", 256),
+    ("k_contract_split.o", r"contract_split_kernelILi256ELi64ELi4ELi4ELi1E", 256),
+    ("k_contract_split.o", r"contract_split_kernelILi64ELi256ELi4ELi4ELi1E", 256),
+    ("k_contract_split.o", r"contract_split_kernelILi128ELi64ELi4ELi2ELi1E", 256),
+    # four 32 KB workgroups of four waves, two 64 KB ones of eight: four waves per SIMD
+    ("k_contract_split.o", r"contract_split_kernelILi64ELi64ELi2ELi2ELi1E", 128),
+    ("k_contract_split.o", r"contract_split_kernelILi64ELi64ELi2ELi2ELi2E", 128),
+    # three 48 KB workgroups of four waves
+    ("k_contract_split.o", r"contract_split_kernelILi64ELi32ELi2ELi2ELi2E", 168),
+    # one 96 KB workgroup of eight waves
+    ("k_contract_split.o", r"contract_split_kernelILi64ELi32ELi2ELi2ELi4E", 256),
+    # 64 channels x 64 pixels a wave: two waves per SIMD
+    ("k_direct.o", r"direct_split_kernelILi[124]E", 256),
+    # four 40 KB workgroups of four waves per CU; at L = 13 two
+    ("k_oaa.o", r"oaa_inverse_strip_kernelILi5E", 128),
+    ("k_oaa.o", r"oaa_inverse_strip_kernelILi9E", 128),
+    ("k_oaa.o", r"oaa_inverse_strip_kernelILi13E", 256),
     # four 128-thread workgroups (L = 32) or two 256-thread ones: two waves per SIMD
     ("k_forward.o", r"forward_band_kernelILi32ELi8ELi16E", 256),
     ("k_forward.o", r"forward_band_kernelILi16ELi32ELi8E", 128),
