@@ -1,8 +1,8 @@
 // fp32 values as sums of three bf16 parts, for matrix products on the bf16
 // matrix instruction with fp32 results: v = h + m + l exactly (8 significand
-// bits each, rounded to nearest, so |m| <= 2^-9 |v| and |l| <= 2^-18 |v|).
-// The six part products down to 2^-18 (kSplitA, kSplitB: smallest first)
-// leave out less than 2^-26 of a product.
+// bits each, rounded to nearest, so |m| <= 2^-8 |v| and |l| <= 2^-17 |v|).
+// The six part products down to 2^-17 (kSplitA, kSplitB: smallest first)
+// leave out m l', l m' and l l', together below 1.01 * 2^-24 of a product.
 #pragma once
 
 #include <hip/hip_runtime.h>

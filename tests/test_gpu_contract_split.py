@@ -6,10 +6,13 @@ that leave whole blocks of padding, and the two slots of real bins, against
 the float64 channel sum of the GPU's own spectra.
 
 Tolerance.  An operand is its three bf16 parts exactly, and what six of the
-nine part products leave out is below 2^-26 of a product.  Each block of 16
-channels is summed by six matrix instructions and added in fp32, and at most 3
-further additions join the wave groups' sums.  With each of those roundings
-below 2^-23 of the sum of absolute products so far,
+nine part products leave out is below 1.01 * 2^-24 of a product, so at most
+1.43 * 2^-24 of a complex one.  Each block of 16 channels is summed by six
+matrix instructions, and then added in fp32 or, in wave groups, not; at most 3
+further additions join the groups' sums.  With each of those roundings below
+2^-23 of the sum of absolute products so far, a single group of ceil(cin / 16)
+blocks is within 7 of them a block and the products left out, groups within 6 a
+block, 3 and the products left out:
     |Y - ref| <= (7 ceil(cin / 16) + 3) 2^-23 (|W| |X|).
 """
 import numpy as np

@@ -4,9 +4,9 @@ around 32 and 16, one, two and four waves of output channels, and inputs that
 are not finite.
 
 Tolerance.  The operands' three bf16 parts are exact and the part products
-left out are below 2^-26 of a product; each tap and group of 32 channels is
-summed by six matrix instructions and added in fp32, each rounding below 2^-23
-of the sum of absolute products so far:
+left out are below 1.01 * 2^-24 of a product; each tap and group of 32 channels
+is summed by six matrix instructions and added in fp32, and the bias once, each
+rounding below 2^-23 of the sum of absolute products so far:
     |y - ref| <= (7 ceil(cin / 32) K^2 + 2) 2^-23 (|w| * |x| + |b|).
 """
 import numpy as np
