@@ -16,6 +16,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kSplitA[6] = {2, 0, 1, 1, 0, 0}, kSplitB[6] = {0, 2, 1, 0, 1, 0};
@@ -48,16 +49,20 @@ __device__ __forceinline__ floatx4 mfma_bf16(u32x4 a, u32x4 b, floatx4 c) {
 // tile again on the fp32 instruction.
 constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
 
-// Whether all N values of the wave are finite, the same in every lane.
+// Whether all values of the wave are finite, the same in every lane.
 template <int N>
-__device__ __forceinline__ bool all_finite(const floatx4* a) {
-    float top = 0.f;
+__device__ __forceinline__ bool all_finite(const floatx4 (&a)[N]) {
+    // (four chains: the last waves of a launch have nothing else to run)
+    floatx4 top = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        top = vmax3(top, __builtin_fabsf(a[i][0]), __builtin_fabsf(a[i][1]));
-        top = vmax3(top, __builtin_fabsf(a[i][2]), __builtin_fabsf(a[i][3]));
-    }
-    return __ballot(!(top < __builtin_inff())) == 0;
+    for (int i = 0; i < N; i += 2)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) top[r] = vmax3(top[r], __builtin_fabsf(a[i][r]), __builtin_fabsf(a[i + 1][r]));
+    return __ballot(!(vmax(vmax(top[0], top[1]), vmax(top[2], top[3])) < __builtin_inff())) == 0;
+}
+template <int M, int N>
+__device__ __forceinline__ bool all_finite(const floatx4 (&a)[M][N]) {
+    return all_finite(reinterpret_cast<const floatx4 (&)[M * N]>(a));
 }
 
 }  // namespace fftsplit

@@ -6,8 +6,9 @@
 //
 // This is the form on the fp32 matrix instruction.  Most plans run
 // contract_split_kernel (k_contract_split.hip) instead, faster and closer to
-// the exact sums; this one runs where it is as fast (choose_contract_split in
-// plan.cpp) or FFTSPLIT_CONTRACT_TILE, FFTSPLIT_CONTRACT_PREFETCH or
+// the exact sums; this one runs where choose_contract_split (plan.cpp) leaves a
+// plan to it (an odd multiple of 32 patches, three or four channel blocks in a
+// small grid) or FFTSPLIT_CONTRACT_TILE, FFTSPLIT_CONTRACT_PREFETCH=1..3 or
 // FFTSPLIT_CONTRACT_SPLIT=0 asks for it.  The layouts, the grid order and the
 // cache policies are the same.
 //

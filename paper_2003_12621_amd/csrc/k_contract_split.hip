@@ -17,11 +17,13 @@
 // tile again on the fp32 instruction, with contract_kernel's products and order
 // (bf16_split.hpp): infinities and NaN come out as there.
 //
-// A complex value (re, im) is one dword of two bf16, and the two sit side by
-// side along the matrix instruction's reduction (k = 2 ci, 2 ci + 1), so
-//     Re Y = sum (Wr, Wi) . (Xr, -Xi),   Im Y = sum (Wr, Wi) . (Xi, Xr):
-// the patch operand's parts are made in both arrangements (one conversion
-// each: the sign is a source modifier), the filter's once, and a reduction
+// The complex product is real along the matrix instruction's reduction, where a
+// lane's four channels c are four dwords, each a pair of channels:
+//     filter operand            (Wr01, Wr23, Wi01, Wi23)
+//     patch operand for Re Y    (Xr01, Xr23, -Xi01, -Xi23)
+//     patch operand for Im Y    (Xi01, Xi23, Xr01, Xr23),
+// so the patch parts are converted once and only negated (one bit operation a
+// pair) for Re Y, whose operand overlaps the other one's registers.  A reduction
 // step of v_mfma_f32_16x16x32_bf16 is 16 input channels, one channel block.
 // Operand layout (64 lanes, lane l):
 //     A[i][k]: i = l % 16, k = 8 (l / 16) + 0..7     (channels 4 (l / 16) + 0..3)
@@ -33,25 +35,28 @@
 //
 // A workgroup tile is BM channels x BN patches of one bin, wave tiles of
 // 16 TM x 16 TN; channel blocks are loaded one ahead straight into LDS as
-// fp32 and split after the LDS read.  At 64 x 64 a wave issues 464 vector
-// instructions of splits, 64 of them for the scale (and 128 additions where a block is summed from zero)
-// beside 384 matrix instructions of 16 cycles per channel block, which two
-// waves per SIMD overlap.  With KG > 1, KG wave groups take the channel blocks
-// in turn and add their sums through LDS: more waves on a compute unit that
-// has one workgroup (small grids, where a wave's chain of LDS read, split and
-// product is what takes the time).
+// fp32 and split after the LDS read.  At 64 x 64 a wave issues 440 vector
+// instructions of splits, 64 of them for the scale (and 128 additions where a
+// block is summed from zero), beside 192 matrix instructions of 16 cycles per
+// channel block; two waves per SIMD overlap them in part.  (With (re, im) dwords
+// the patch parts were converted twice, 96 of 192 conversions: 32x512x28^2 187
+// us, in channel pairs 176; 16x256x56^2 K=5 105, 100.)  With KG > 1, KG wave
+// groups take the channel blocks in turn and add their sums through LDS: more
+// waves on a compute unit that has one workgroup (small grids, where a wave's
+// chain of LDS read, split and product is what takes the time).
 //
 // What bounds it (MI355X): the matrix cores, whose clock falls to 2.0 GHz
 // under it (2.4 under the fp32 kernel; a loop of the instruction alone
 // reaches 1745 TFLOP/s at 32x32x16 and 2040 at 16x16x32, hence that shape),
 // then the vector work and, with few patches, HBM.  Against the fp32 kernel,
-// whole launches in us (algorithmic rate at 8 flops per complex product):
-//     32x256x56^2, 512 patches            217 -> 171  (157 -> 201 TFLOP/s)
-//     32x512x28^2, 128 patches            217 -> 175
-//     32x128x112^2, 2048 patches          238 -> 177
-//     16x256x56^2 K=5, 64 patches         119 -> 100  (4.0 TB/s)
-//     32x64x224^2, 8192 patches           283 -> 240  (4.5 TB/s)
-//     1x512x28^2 at L = 8, 25 patches      34 ->  22
+// whole launches in us (algorithmic rate at 8 flops per complex product; one
+// run, other boxes are up to 10 % slower):
+//     32x256x56^2, 512 patches            214 -> 158  (161 -> 217 TFLOP/s)
+//     32x512x28^2, 128 patches            207 -> 160
+//     32x128x112^2, 2048 patches          228 -> 162
+//     16x256x56^2 K=5, 64 patches         112 ->  93  (4.3 TB/s)
+//     32x64x224^2, 8192 patches           254 -> 206  (5.2 TB/s)
+//     1x512x28^2 at L = 8, 25 patches      36 ->  25
 // Tried without gain: the vector work interleaved with the matrix
 // instructions by the scheduler instead of two waves overlapping, two and three
 // stages ahead, and a priority for one of a compute unit's two workgroups.
@@ -104,20 +109,6 @@ __device__ __forceinline__ uint64_t uniform_address(const void* p) {
     const unsigned lo = unsigned(__builtin_amdgcn_readfirstlane(int(unsigned(a))));
     const unsigned hi = unsigned(__builtin_amdgcn_readfirstlane(int(unsigned(a >> 32))));
     return uint64_t(lo) | uint64_t(hi) << 32;
-}
-
-// The patch operand, for Re Y and for Im Y: the parts of (re, -im) and of
-// (im, re), or of (re, 0) and (0, im) in a slot of two real bins.
-template <bool PACKED>
-__device__ __forceinline__ void split_patch(float re, float im, unsigned (&br)[3], unsigned (&bi)[3]) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        const unsigned v = pack_bf16(im, re);
-        br[q] = PACKED ? v >> 16 : pack_bf16(re, -im);
-        bi[q] = PACKED ? v << 16 : v;
-        im -= __uint_as_float(v << 16);
-        re -= __uint_as_float(v & 0xffff0000u);
-    }
 }
 
 template <int BM, int BN, int TM, int TN>
@@ -214,16 +205,21 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
 #pragma unroll
         for (int p = 0; p < TM / 2; ++p)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const float4 v = *reinterpret_cast<const float4*>(sw + c * BM + 32 * p);
-                unsigned q0[3], q1[3];
-                split3(v.x * kSplitScale, v.y * kSplitScale, q0);
-                split3(v.z * kSplitScale, v.w * kSplitScale, q1);
+            for (int c = 0; c < 4; c += 2) {
+                const float4 u = *reinterpret_cast<const float4*>(sw + c * BM + 32 * p);
+                const float4 v = *reinterpret_cast<const float4*>(sw + (c + 1) * BM + 32 * p);
+                unsigned re[2][3], im[2][3];
+                split3(u.x * kSplitScale, v.x * kSplitScale, re[0]);
+                split3(u.y * kSplitScale, v.y * kSplitScale, im[0]);
+                split3(u.z * kSplitScale, v.z * kSplitScale, re[1]);
+                split3(u.w * kSplitScale, v.w * kSplitScale, im[1]);
 #pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    a[q][2 * p][c] = q0[q];
-                    a[q][2 * p + 1][c] = q1[q];
-                }
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        a[q][2 * p + e][c / 2] = re[e][q];
+                        a[q][2 * p + e][2 + c / 2] = im[e][q];
+                    }
             }
 #pragma unroll
         for (int p = 0; p < TN / 2; ++p) {
@@ -233,17 +229,29 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const int j = 2 * p + e;
+                // (im, re, -im) of both channel pairs; in a slot of two real
+                // bins (0, re, 0) and (0, im)
+                u32x8 x[3];
                 u32x4 br[3], bi[3];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    unsigned qr[3], qi[3];
-                    split_patch<decltype(packed)::value>((e ? v[c].z : v[c].x) * kSplitScale,
-                                                         (e ? v[c].w : v[c].y) * kSplitScale, qr, qi);
+                for (int c = 0; c < 4; c += 2) {
+                    unsigned re[3], im[3];
+                    split3((e ? v[c].z : v[c].x) * kSplitScale, (e ? v[c + 1].z : v[c + 1].x) * kSplitScale, re);
+                    split3((e ? v[c].w : v[c].y) * kSplitScale, (e ? v[c + 1].w : v[c + 1].y) * kSplitScale, im);
+                    constexpr bool two_real = decltype(packed)::value;
 #pragma unroll
                     for (int q = 0; q < 3; ++q) {
-                        br[q][c] = qr[q];
-                        bi[q][c] = qi[q];
+                        x[q][c / 2] = two_real ? 0u : im[q];
+                        x[q][2 + c / 2] = re[q];
+                        x[q][4 + c / 2] = two_real ? 0u : im[q] ^ 0x80008000u;
+                        x[q][6 + c / 2] = im[q];
                     }
+                }
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    bi[q] = decltype(packed)::value ? __builtin_shufflevector(x[q], x[q], 0, 1, 6, 7)
+                                                    : __builtin_shufflevector(x[q], x[q], 0, 1, 2, 3);
+                    br[q] = __builtin_shufflevector(x[q], x[q], 2, 3, 4, 5);
                 }
                 // Smallest part products first; `fresh`: the block's sum from
                 // zero, then one fp32 addition.
@@ -273,7 +281,7 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
         const int s = it * KG + group;
         if (s < nstage) dma_stage(s, buffer(it));
     };
-    // Whether the wave's sums are finite (bf16_split.hpp), and stored.
+    // Stores the wave's sums and tells whether they are finite (bf16_split.hpp).
     auto run = [&](auto packed) __attribute__((always_inline)) {
         floatx4 accR[TM][TN], accI[TM][TN];
 #pragma unroll
@@ -343,8 +351,6 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
         }
 
         const int lane = fresh_lane(), quad = lane >> 4, col = lane & 15;
-        if (!all_finite<TM * TN>(&accR[0][0]) || !all_finite<TM * TN>(&accI[0][0])) return false;
-
         // Output spectra (patch-group-major): D register r of lane (quad,
         // col) is row 4 quad + r, column col of its 16 x 16 block, so a lane
         // holds pairs of neighbouring patches: 16-byte stores, 16 lanes a row.
@@ -363,21 +369,24 @@ __global__ __launch_bounds__((KG * SplitShape<BM, BN, TM, TN>::NT), 2) void cont
                                                 accR[i][j + 1][r] * kSplitUnscale, accI[i][j + 1][r] * kSplitUnscale), ry,
                                     voff, unsigned(32 * (i / 2) + 2 * r + i % 2) * cs8);
         }
-        return true;
+        return all_finite(accR) && all_finite(accI);
     };
     // one loop for each kind of bin (a branch inside the loop would merge the
     // accumulators of its two sides by copies)
     const bool two_real = f >= nbins - npacked;
     if (two_real ? run(std::true_type{}) : run(std::false_type{})) return;
 
-    // The wave's tile on the fp32 instruction, operands from memory: the
-    // products and the order of contract_kernel with three real products.
+    // The wave's tile again on the fp32 instruction, operands from memory: the
+    // products and the order of contract_kernel with three real products.  It
+    // takes the place of what was stored.
+    __builtin_amdgcn_s_waitcnt(0);
     const int krow = fresh_lane() >> 5, l32 = fresh_lane() & 31;
     for (int blk = 0; blk < (TM / 2) * (TN / 2); ++blk) {
         const int co = co0 + wm * (16 * TM) + blk / (TN / 2) * 32, t = t0 + wn * (16 * TN) + blk % (TN / 2) * 32;
         floatx16 p1, p2, p3;
 #pragma unroll
         for (int r = 0; r < 16; ++r) p1[r] = p2[r] = p3[r] = 0.f;
+#pragma unroll 1
         for (int c0 = 0; c0 < cin; c0 += 2) {
             const int c = c0 + krow;
             float2 a = make_float2(0.f, 0.f), b = a;

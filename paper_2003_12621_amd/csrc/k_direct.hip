@@ -160,12 +160,12 @@ __global__ __launch_bounds__(256) void direct_kernel(const float* __restrict__ x
 // finite computes its block again on the fp32 instruction, in direct_kernel's
 // order.
 // Bound: the matrix cores (clock 2.0 GHz under them) and the vector work
-// beside them.  16x256x56^2 -> 256, K = 5: 1754 us on the fp32 instruction,
-// 945 us here (174 TFLOP/s of the convolution's operations); 8x128x112^2
-// K = 3 327 -> 204 us, 32x512x28^2 1265 -> 704 us.  Error against float64
-// 1.0e-6 -> 2.8e-7 on the first: each tap's 32 channels are summed from zero
-// and added in fp32 (with the running sum in the matrix unit it was 1.2e-6,
-// at 896 us).
+// beside them.  16x256x56^2 -> 256, K = 5: 1761 us on the fp32 instruction,
+// 973 us here (169 TFLOP/s of the convolution's operations; 955 without the
+// scale); 8x128x112^2 K = 3 324 -> 209 us, 32x512x28^2 1264 -> 728 us.  Error
+// against float64 1.0e-6 -> 2.8e-7 on the first: each tap's 32 channels are
+// summed from zero and added in fp32 (with the running sum in the matrix unit it
+// was 1.2e-6, 5 % faster).
 template <int NW>
 __global__ __launch_bounds__(64 * NW, 2) void direct_split_kernel(
     const float* __restrict__ x, const float* __restrict__ wd, const float* __restrict__ bias, float* __restrict__ y,
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(64 * NW, 2) void direct_split_kernel(
         if (relu) v = vmax(v, 0.f);
         buf_store_f32(v, ry, co < cout && px != kOutOfRange ? px + unsigned(co * hw) * 4u : kOutOfRange, 0);
     };
-    if (all_finite<16>(&acc[0][0])) {
+    if (all_finite(acc)) {
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
             const unsigned px = pixel(16 * n + col);

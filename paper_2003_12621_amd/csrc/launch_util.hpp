@@ -43,7 +43,8 @@ inline FastDiv fast_div(int d) {
     return FastDiv{unsigned((1ULL << (31 + l)) / unsigned(d) + 1), l - 1};
 }
 
-// Allows a kernel to use more than the default dynamic LDS once per process.
+// Allows a kernel to use `bytes` of dynamic LDS on the current device (64 KB
+// need no permission).
 template <typename K>
 inline hipError_t allow_dynamic_lds(K kernel, int bytes) {
     if (bytes <= 64 * 1024) return hipSuccess;

@@ -40,7 +40,10 @@ static bool mul_ok(size_t a, size_t b, size_t* out) {
 }
 
 // Effective rates of the cost model (bytes/s and flop/s) -- deliberately
-// conservative fractions of the 8 TB/s HBM and 157 TFLOP/s fp32 matrix peaks.
+// conservative fractions of the 8 TB/s HBM and 157 TFLOP/s fp32 matrix peaks,
+// fitted with the contraction on the fp32 instruction.  The bf16 one runs at
+// 160-230 TFLOP/s, so the model overstates the contraction's share; the tiles it
+// picks have not been fitted again.
 static constexpr double kModelBandwidth = 5.0e12;
 static constexpr double kModelMatrixRate = 100.0e12;
 
