@@ -10,9 +10,10 @@
 // error against float64 was up to 30 % above the fp32 kernel's on a network's
 // activations (positive, correlated; below it on others).  In the last 3/8 of
 // the channels, where the sum is large, a block is therefore summed from zero
-// and then added in fp32.  Error over the layers of a VGG-16 stack at batch 4
-// and 32, against the fp32 kernel's: 0.67-0.96 of it; with every block from
-// zero 0.36-0.70, but 4-8 % slower.  Operands are scaled by a power of two, so
+// and then added in fp32.  Error over the layers of a VGG-16 stack at batch 1, 4
+// and 32, against the fp32 kernel's: 0.39-0.81 of it (0.67-0.96 with (re, im)
+// pairs along the reduction, see below, and then 0.36-0.70 with every block from
+// zero, 4-8 % slower).  Operands are scaled by a power of two, so
 // that no part underflows, and a wave whose sums are not all finite computes its
 // tile again on the fp32 instruction, with contract_kernel's products and order
 // (bf16_split.hpp): infinities and NaN come out as there.
